@@ -197,9 +197,13 @@ int lbm_set_plane_pad(lbm_ctx_t *ctx, int32_t pad_bytes);
  * bytes (-1 for a context that takes none); either pointer may be NULL. */
 int lbm_get_layout(const lbm_ctx_t *ctx, int64_t *plane_stride, int32_t *pad_bytes);
 
-/* Force a launch shape by index (0 = default); LBM_EINVAL if out of range.
- * For a batch, a shape with another tile size rebuilds the tile tables (a
- * device allocation). */
+/* Force a launch shape by index; LBM_EINVAL if out of range.  Shape 0 takes
+ * one step per launch and runs everywhere; a single D2Q9 lattice starts with
+ * the shape the library estimates to be the fastest without set-up (shape 0,
+ * or for small and medium lattices one that takes several steps per launch
+ * in on-chip windows), every other context with shape 0.  For a batch, a
+ * shape with another tile size rebuilds the tile tables (a device
+ * allocation). */
 int lbm_set_variant(lbm_ctx_t *ctx, int32_t variant);
 
 /* Number of launch shapes (for lbm_set_variant) and a short description. */
@@ -208,7 +212,9 @@ const char *lbm_variant_name(const lbm_ctx_t *ctx, int32_t variant);
 
 /* Steps one launch of a shape takes at most: 1; 2 for the temporally blocked
  * D2Q9 shapes (MinxEnt4, single lattices and batches), which compute one
- * step into on-chip memory and the next from there; 16, 32, 64 or 256 for
+ * step into on-chip memory and the next from there; up to 64 for the D2Q9
+ * on-chip window shapes (single lattices, every rule; as many as a window
+ * holds at the lattice's size); 16, 32, 64 or 256 for
  * the D1Q3 shapes that keep 1024-node segments on chip for that many steps.
  * HBM then sees one read and one write of every population per launch.
  * Results are bitwise equal to single steps, status records included;
@@ -261,7 +267,8 @@ void lbm_free(lbm_ctx_t *ctx);
  *                  ignored and may be NULL for D1Q3.  Every node starts at the
  *                  polynomial equilibrium of its fields, lid nodes at the lid
  *                  equilibrium (the state lbm_init sets).
- *   nsteps:        steps to run (>= 0), in the one-step launch shape 0.
+ *   nsteps:        steps to run (>= 0), in the shape a new context of these
+ *                  parameters starts with (see lbm_set_variant).
  *   rho_out, ux_out, uy_out: DEVICE arrays of nx*ny doubles receiving the
  *                  moments of the final state, as lbm_moments writes them;
  *                  any may be NULL; they may alias the inputs.

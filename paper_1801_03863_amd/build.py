@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblbm.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["kernels.hip", "runtime.hip"]
+SOURCES = ["kernels.hip", "window.hip", "runtime.hip"]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950",
@@ -38,7 +38,7 @@ def hipcc() -> str:
 
 # The sources of the device kernels: the launch shapes the autotuner times
 # and caches are defined here, so a cache entry stays valid while they do.
-KERNEL_SOURCES = ["collide.hpp", "kernels.hip", "kernels.hpp"]
+KERNEL_SOURCES = ["collide.hpp", "device.hpp", "kernels.hip", "kernels.hpp", "window.hip"]
 
 
 def source_id() -> str:
@@ -52,7 +52,7 @@ def source_id() -> str:
     return h.hexdigest()[:12]
 
 
-def build_library(verbose: bool = False, jobs: int = 2) -> str:
+def build_library(verbose: bool = False, jobs: int = 3) -> str:
     """Compile every HIP source for gfx950 and link liblbm.so (always rebuilds)."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     cc = hipcc()

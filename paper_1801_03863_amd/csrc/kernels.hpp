@@ -37,6 +37,11 @@ struct Inst {
     int64_t stop;    // batched: the instance takes no step from this step index on
 };
 
+// Tile of the on-chip window shapes: tw x th nodes, gx x gy tiles.
+struct WindowTile {
+    int32_t tw, th, gx, gy;
+};
+
 // Everything a step launch needs besides the buffers.
 struct StepArgs {
     const Inst *inst;       // device table (batched) -- or nullptr
@@ -54,21 +59,37 @@ struct StepArgs {
     float fp16_scale;       // FP16DEV: 2^k
     float fp16_iscale;      // 2^-k
     int32_t max_steps;      // shapes taking several steps per launch: steps this launch takes
+    WindowTile win;         // on-chip window shapes
 };
 
 // Host-side launchers (return hipError_t of the launch).
 int d2q9_variant_count(int coll);
-const char *d2q9_variant_name(int variant);
-// Steps one launch of a single-lattice D2Q9 shape takes (1, or 2 for the
-// temporally blocked shapes; StepArgs::max_steps = 1 makes one of those take
-// a single step), and the host-side set-up a shape needs before its first
-// launch (call outside stream capture).
+const char *d2q9_variant_name(int coll, int variant);
+// Steps one launch of a single-lattice D2Q9 shape takes at most (1; 2 for the
+// temporally blocked shapes; more for the on-chip window shapes, where a
+// lattice may allow fewer: d2q9_window_plan; StepArgs::max_steps sets fewer),
+// whether it is a window shape, and the host-side set-up a shape needs before
+// its first launch (call outside stream capture).
 int d2q9_variant_steps(int coll, int variant);
+bool d2q9_variant_window(int coll, int variant);
+// Shape a single lattice runs in unless another is set: the fastest by the
+// estimates above its definition, among shape 0 and the window shapes (none
+// of which needs set-up).
+int d2q9_default_variant(int storage, int coll, int nx, int ny, int bc);
 hipError_t prepare_d2q9_variant(int st, int coll, int variant);
 hipError_t launch_d2q9_step(int storage, int coll, int variant, const void *src, void *dst,
                             const StepArgs &a, hipStream_t s);
 hipError_t launch_d2q9_batch_step(int storage, int coll, int variant, const void *src, void *dst,
                                   const StepArgs &a, hipStream_t s);
+// On-chip window shapes (window.hip).  Nodes a window may hold; the tile for
+// launches of k steps of one lattice (false if no window of k steps fits)
+// with its estimated microseconds per step; and the launch (StepArgs::win holds the
+// tile, max_steps at most the k it was planned for).
+constexpr int kWindowCus = 256;  // compute units the tiles are spread over
+int d2q9_window_cap(int storage);
+bool d2q9_window_plan(int storage, int coll, int nx, int ny, int bc, int k, WindowTile *tile,
+                      double *us_per_step);
+hipError_t launch_d2q9_window(int storage, int coll, const void *src, void *dst, const StepArgs &a, hipStream_t s);
 int d1q3_variant_count();
 const char *d1q3_variant_name(int variant);
 int d1q3_variant_steps(int variant);  // steps one launch takes at most (K-step shapes; StepArgs::max_steps sets fewer)

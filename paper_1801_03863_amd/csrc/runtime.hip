@@ -161,6 +161,8 @@ struct lbm_ctx {
     int64_t *d_step_base = nullptr;
     bool base_synced = false;
     int variant = 0;
+    int spl = 1;             // steps one launch of the current shape takes at most
+    lbm::WindowTile win{};   // tile of the current shape if it is an on-chip window shape
     int graph_chunk = 0;
     int32_t pad = -1;        // plane pad in bytes; -1: the context takes none
     int64_t plane_base = 0;  // plane length before the pad (elements)
@@ -320,6 +322,7 @@ lbm::StepArgs step_args(const lbm_ctx *c, DevStatus *status, int64_t step, const
     a.fp16_scale = c->scale;
     a.fp16_iscale = c->iscale;
     a.max_steps = 2;  // launchers of multi-step shapes set the count they need
+    a.win = c->win;
     return a;
 }
 
@@ -334,13 +337,43 @@ hipError_t launch_step(const lbm_ctx *c, int variant, const void *src, void *dst
     return lbm::launch_d1q3_step(c->storage, variant, src, dst, a, s);
 }
 
+// Tile of on-chip window shape v for a lattice, and the steps a launch
+// takes: the shape's count, halved until a window of that many steps fits
+// (one step always does: its window is the tile).
+int window_plan(const lbm_params_t &p, int v, lbm::WindowTile *tile)
+{
+    const int st = storage_of(p.precision);
+    for (int k = lbm::d2q9_variant_steps(p.collision, v); k > 1; k /= 2)
+        if (lbm::d2q9_window_plan(st, p.collision, p.nx, p.ny, p.bc, k, tile, nullptr)) return k;
+    *tile = lbm::WindowTile{std::min(p.nx, 32), std::min(p.ny, 28), 0, 0};
+    tile->gx = (p.nx + tile->tw - 1) / tile->tw;
+    tile->gy = (p.ny + tile->th - 1) / tile->th;
+    return 1;
+}
+
 // Steps one launch of shape v takes at most: 2 for the temporally blocked
-// D2Q9 shapes, up to 256 for the K-step D1Q3 shapes, else 1.
+// D2Q9 shapes, what fits for the on-chip window shapes, up to 256 for the
+// K-step D1Q3 shapes, else 1.
 int launch_steps(const lbm_ctx *c, int v)
 {
+    if (v == c->variant) return c->spl;
     if (c->b != 9) return c->batch ? lbm::batch_variant_steps(3, v) : lbm::d1q3_variant_steps(v);
     if (c->batch) return v == c->lds_variant ? 1 : lbm::batch_variant_steps(9, v);
+    if (lbm::d2q9_variant_window(c->p.collision, v)) {
+        lbm::WindowTile tile;
+        return window_plan(c->p, v, &tile);
+    }
     return lbm::d2q9_variant_steps(c->p.collision, v);
+}
+
+// Make v the context's shape (host bookkeeping only).
+void use_variant(lbm_ctx *c, int v)
+{
+    c->variant = -1;  // so that launch_steps() plans anew
+    c->win = lbm::WindowTile{};
+    c->spl = launch_steps(c, v);
+    if (!c->batch && c->b == 9 && lbm::d2q9_variant_window(c->p.collision, v)) window_plan(c->p, v, &c->win);
+    c->variant = v;
 }
 
 // Launch `n` steps (at most the shape's steps per launch) of shape v from
@@ -559,6 +592,8 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
             return rc;
         }
     }
+    if (!batch && c->b == 9)
+        use_variant(c, lbm::d2q9_default_variant(c->storage, c->p.collision, c->p.nx, c->p.ny, c->p.bc));
     CK(lbm::launch_clear_status(c->d_status, n, c->stream));
     CK(lbm::launch_clear_status(c->d_status_scratch, n, c->stream));
     CK(lbm::launch_set_step_base(c->d_step_base, 0, c->stream));
@@ -713,7 +748,7 @@ int lbm_set_variant(lbm_ctx_t *c, int32_t v)
     if (c->batch && c->b == 9 && v != c->lds_variant)
         HIPCHK(lbm::prepare_batch_variant(c->storage, c->p.collision, v));
     if (c->b == 3) HIPCHK(lbm::prepare_d1q3_variant(c->storage, c->batch, v));
-    c->variant = v;
+    use_variant(c, v);
     if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, v) != c->tile_nodes)
         return build_tiles(c, lbm::batch_tile_nodes(c->b, v));
     return LBM_OK;
@@ -764,7 +799,7 @@ const char *lbm_variant_name(const lbm_ctx_t *c, int32_t v)
     if (!c) return "?";
     if (c->batch && v == c->lds_variant && v >= 0) return "batch persistent, lattices resident in LDS";
     if (c->batch) return lbm::batch_variant_name(c->b, v);
-    return c->b == 9 ? lbm::d2q9_variant_name(v) : lbm::d1q3_variant_name(v);
+    return c->b == 9 ? lbm::d2q9_variant_name(c->p.collision, v) : lbm::d1q3_variant_name(v);
 }
 
 int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
@@ -1056,15 +1091,19 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
     a.bc = p->bc;
     a.fp16_scale = scale;
     a.fp16_iscale = iscale;
-    a.max_steps = 1;
+    // The shape a context would start with: none of those needs set-up or
+    // memory, so all of them run here and under capture.
+    const int v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc) : 0;
+    const int spl = b == 9 && lbm::d2q9_variant_window(p->collision, v) ? window_plan(*p, v, &a.win) : 1;
     int cur = 0;
-    for (int64_t i = 0; i < nsteps; ++i) {
+    for (int64_t i = 0; i < nsteps;) {
         a.step = i;
-        // Shape 0: one step per launch, every node once per step.
-        hipError_t e = (b == 9) ? lbm::launch_d2q9_step(storage, p->collision, 0, buf[cur], buf[cur ^ 1], a, s)
-                                : lbm::launch_d1q3_step(storage, 0, buf[cur], buf[cur ^ 1], a, s);
+        a.max_steps = (int)std::min<int64_t>(spl, nsteps - i);
+        hipError_t e = (b == 9) ? lbm::launch_d2q9_step(storage, p->collision, v, buf[cur], buf[cur ^ 1], a, s)
+                                : lbm::launch_d1q3_step(storage, v, buf[cur], buf[cur ^ 1], a, s);
         if (e != hipSuccess) return hip_fail(e, "lbm_run_noalloc step");
         cur ^= 1;
+        i += a.max_steps;
     }
     HIPCHK(lbm::launch_gather(b, storage, inst[0], p->bc, buf[cur], rho_out, ux_out, b == 9 ? uy_out : nullptr,
                               nullptr, iscale, s));
