@@ -200,8 +200,8 @@ int lbm_get_layout(const lbm_ctx_t *ctx, int64_t *plane_stride, int32_t *pad_byt
 /* Force a launch shape by index; LBM_EINVAL if out of range.  Shape 0 takes
  * one step per launch and runs everywhere; a single D2Q9 lattice starts with
  * the shape the library estimates to be the fastest without set-up (shape 0,
- * or for small and medium lattices one that takes several steps per launch
- * in on-chip windows), every other context with shape 0.  For a batch, a
+ * or one that takes several steps per launch: on-chip windows for small and
+ * medium lattices, register pipelines beyond), every other context with shape 0.  For a batch, a
  * shape with another tile size rebuilds the tile tables (a device
  * allocation). */
 int lbm_set_variant(lbm_ctx_t *ctx, int32_t variant);
@@ -214,8 +214,10 @@ const char *lbm_variant_name(const lbm_ctx_t *ctx, int32_t variant);
  * D2Q9 shapes (MinxEnt4, single lattices and batches), which compute one
  * step into on-chip memory and the next from there; up to 64 for the D2Q9
  * on-chip window shapes (single lattices, every rule; as many as a window
- * holds at the lattice's size); 16, 32, 64 or 256 for
- * the D1Q3 shapes that keep 1024-node segments on chip for that many steps.
+ * holds at the lattice's size); 2, 3 or 4 for the D2Q9 register pipelines
+ * (single lattices, every rule), which pass each row from step to step in
+ * registers; 16, 32, 64 or 256 for the D1Q3 shapes that keep 1024-node
+ * segments on chip for that many steps.
  * HBM then sees one read and one write of every population per launch.
  * Results are bitwise equal to single steps, status records included;
  * lbm_step() and graph chunks run a remainder as a launch of fewer steps,

@@ -12,7 +12,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblbm.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["kernels.hip", "window.hip", "runtime.hip"]
+# (object name, source, extra flags): pipeline.hip once per collision rule.
+SOURCES = [("kernels", "kernels.hip", []), ("window", "window.hip", [])]
+SOURCES += [("pipeline%d" % co, "pipeline.hip", ["-DLBM_PIPE_CO=%d" % co]) for co in range(5)]
+SOURCES += [("runtime", "runtime.hip", [])]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950",
@@ -38,7 +41,8 @@ def hipcc() -> str:
 
 # The sources of the device kernels: the launch shapes the autotuner times
 # and caches are defined here, so a cache entry stays valid while they do.
-KERNEL_SOURCES = ["collide.hpp", "device.hpp", "kernels.hip", "kernels.hpp", "window.hip"]
+KERNEL_SOURCES = ["collide.hpp", "device.hpp", "kernels.hip", "kernels.hpp", "pipeline.hip", "pipeline.hpp",
+                  "window.hip"]
 
 
 def source_id() -> str:
@@ -52,15 +56,16 @@ def source_id() -> str:
     return h.hexdigest()[:12]
 
 
-def build_library(verbose: bool = False, jobs: int = 3) -> str:
+def build_library(verbose: bool = False, jobs: int = 4) -> str:
     """Compile every HIP source for gfx950 and link liblbm.so (always rebuilds)."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     cc = hipcc()
     flags = HIP_FLAGS + ["-DLBM_SOURCE_ID=\"%s\"" % source_id()]
 
-    def compile_one(src):
-        obj = os.path.join(BUILD_DIR, src + ".o")
-        cmd = [cc, *flags, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(item):
+        name, src, extra = item
+        obj = os.path.join(BUILD_DIR, name + ".o")
+        cmd = [cc, *flags, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)

@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <stdint.h>
 
 #include "device.hpp"
@@ -1243,12 +1244,26 @@ constexpr Shape kShapes[] = {
     {0, 0, 1, 0, "on-chip windows, up to 8 steps per launch", 8},
     {0, 0, 1, 0, "on-chip windows, up to 16 steps per launch", 16},
     {0, 0, 1, 0, "on-chip windows, up to 64 steps per launch", 64},
+    {0, 0, 1, 0, "register pipeline, 2 steps per launch", 2},
+    {0, 0, 1, 0, "register pipeline, 3 steps per launch", 3},
+    {0, 0, 1, 0, "register pipeline, 4 steps per launch", 4},
+    {0, 8, 1, 0, "register pipeline, 2 steps per launch, 64x8 tiles", 2},
+    {0, 8, 1, 0, "register pipeline, 3 steps per launch, 64x8 tiles", 3},
+    {0, 8, 1, 0, "register pipeline, 4 steps per launch, 64x8 tiles", 4},
+    {0, 16, 1, 0, "register pipeline, 2 steps per launch, 64x16 tiles", 2},
+    {0, 16, 1, 0, "register pipeline, 3 steps per launch, 64x16 tiles", 3},
+    {0, 16, 1, 0, "register pipeline, 4 steps per launch, 64x16 tiles", 4},
+    {0, 32, 1, 0, "register pipeline, 2 steps per launch, 64x32 tiles", 2},
+    {0, 32, 1, 0, "register pipeline, 3 steps per launch, 64x32 tiles", 3},
+    {0, 32, 1, 0, "register pipeline, 4 steps per launch, 64x32 tiles", 4},
 };
 
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 constexpr int kMaxGridY = 65535;  // grid y limit; larger tile counts use a 1D grid
-constexpr int kNumWindows = 5;    // the last shapes: on-chip windows, every collision rule
-constexpr int kFirstWindow = kNumShapes - kNumWindows;
+constexpr int kNumPipes = 12;     // the last shapes: register pipeline, every collision rule
+constexpr int kFirstPipe = kNumShapes - kNumPipes;
+constexpr int kNumWindows = 5;    // before them: on-chip windows, every collision rule
+constexpr int kFirstWindow = kFirstPipe - kNumWindows;
 constexpr int kNumOneOther = 3;   // the other collision rules instantiate the first three single-step shapes
 
 // Entry of kShapes of shape v of a collision rule, or -1.
@@ -1745,31 +1760,47 @@ hipError_t gather_st(int lattice, const Inst &in, int bc, const void *buf, doubl
 
 }  // namespace
 
-int d2q9_variant_count(int coll) { return coll == CO_MINXENT4 ? kNumShapes : kNumOneOther + kNumWindows; }
+int d2q9_variant_count(int coll) { return coll == CO_MINXENT4 ? kNumShapes : kNumOneOther + kNumWindows + kNumPipes; }
 int d2q9_variant_steps(int coll, int v)
 {
     const int k = shape_of(coll, v);
     return k >= 0 ? kShapes[k].steps : 1;
 }
-bool d2q9_variant_window(int coll, int v) { return shape_of(coll, v) >= kFirstWindow; }
+bool d2q9_variant_window(int coll, int v)
+{
+    const int k = shape_of(coll, v);
+    return k >= kFirstWindow && k < kFirstPipe;
+}
 
 // One-step launches cost about 4.3 us each up to some 60k nodes and then
 // 3 us + 23 ps per node (FP64, 257^2 to 1000^2: 6.1, 8.4, 10.3, 11.2, 18.5 and
 // 24.9 us at 257, 400, 512, 600, 800 and 1000; FP32 about three quarters of
-// that from 600^2 on).  The window shapes take 1.6 us per step at 32^2, 2.0 at
-// 128^2, 3.6 at 257^2 and 8.1 at 512^2, so they lead up to about 550^2.
+// that from 600^2 on), and the bytes of a step beyond the caches (1400^2 55 us,
+// 2048^2 110 us).  The window shapes take 1.6 us per step at 32^2, 2.0 at
+// 128^2, 3.6 at 257^2 and 8.1 at 512^2, so they lead up to about 550^2; the
+// register pipelines lead from there on (FP64 MinxEnt4 / MRT, us per step:
+// 1000^2 21.6 / 16.5, 2048^2 61 / 50, 4096^2 221 / 157, against 24.9 / 24.1,
+// 110 / 109 and 430 / 432 for one step per launch).
 int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
 {
-    const int first = d2q9_variant_count(coll) - kNumWindows;
-    const double nodes = (double)nx * ny;
-    double best = std::max(4.3, 3.0 + (st == ST_F64 ? 2.3e-5 : 1.7e-5) * nodes);
+    const int windows = d2q9_variant_count(coll) - kNumPipes - kNumWindows;
+    const double nodes = (double)nx * ny, elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
+    double best = std::max({4.3, 3.0 + (st == ST_F64 ? 2.3e-5 : 1.7e-5) * nodes, nodes * 18 * elem / 5.5e6});
     int v = 0;
     for (int k = 0; k < kNumWindows; ++k) {
         WindowTile tile;
         double us = 0;
         if (d2q9_window_plan(st, coll, nx, ny, bc, kShapes[kFirstWindow + k].steps, &tile, &us) && us < best) {
             best = us;
-            v = first + k;
+            v = windows + k;
+        }
+    }
+    for (int k = 0; k < 3; ++k) {  // the shapes whose rows go by the lattice
+        double us = 0;
+        d2q9_pipe_rows(st, coll, nx, ny, kShapes[kFirstPipe + k].steps, &us);
+        if (us < 0.95 * best) {
+            best = us;
+            v = windows + kNumWindows + k;
         }
     }
     return v;
@@ -1777,7 +1808,7 @@ int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
 
 hipError_t prepare_d2q9_variant(int st, int coll, int v)
 {
-    if (d2q9_variant_steps(coll, v) != 2 || d2q9_variant_window(coll, v)) return hipSuccess;
+    if (shape_of(coll, v) >= kFirstWindow || d2q9_variant_steps(coll, v) != 2) return hipSuccess;
     const StepArgs none{};
     switch (st) {
     case ST_F64: return dispatch9t2<ST_F64, CO_MINXENT4>(v, true, nullptr, nullptr, none, nullptr);
@@ -1850,10 +1881,73 @@ const char *batch_variant_name(int lattice, int v)
     return (v >= 0 && v < kNumB9) ? kShapesB9[v].name : "?";
 }
 
+bool d2q9_variant_pipe(int coll, int v) { return shape_of(coll, v) >= kFirstPipe; }
+int d2q9_variant_rows(int coll, int v)
+{
+    const int k = shape_of(coll, v);
+    return k >= kFirstPipe ? kShapes[k].by : 0;
+}
+
+int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
+{
+    const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
+    // Waves per SIMD the kernel's registers allow.
+    const int occ = st == ST_F64 ? (newton ? 6 - k : 7 - k) : (st == ST_F32N64 && newton ? 4 : 6);
+    const double latency = newton ? 1950 : 1000, issue = newton ? 1550 : 700;  // cycles of one collision
+    const double elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
+    const int w = 64 - 2 * (k - 1);
+    const int64_t strips = (nx + w - 1) / w;
+    double best = 0;
+    int rows = 1;
+    for (int h = 1; h <= 48; ++h) {
+        if (h > ny) break;
+        const int64_t blocks = (strips * ((ny + h - 1) / h) + 3) / 4;
+        // Blocks per compute unit: whole while few are resident at once, on
+        // average (and part of a block of tail) when they come and go.
+        const double mean = (double)blocks / kWindowCus, whole = std::ceil(mean);
+        const double r = whole <= 3 && whole <= occ ? whole : mean + 0.6;
+        const double collisions = k * h + k * (k - 1);  // of one wave
+        const double compute = collisions * std::max(latency, r * issue);
+        const double bytes = (double)nx * ny * 9 * elem * (2.1 + 0.6 * k / h);
+        const double us = 4.0 + std::max(compute / 2200, bytes / 5.5e6);
+        if (best == 0 || us < best) {
+            best = us;
+            rows = h;
+        }
+    }
+    if (us_per_step) *us_per_step = best / k;
+    return rows;
+}
+
+namespace {
+hipError_t launch_d2q9_pipe(int st, int coll, const void *src, void *dst, const StepArgs &a_in, hipStream_t s)
+{
+    StepArgs a = a_in;
+    if (a.tile_rows < 1) return hipErrorInvalidValue;
+    const int w = 64 - 2 * (a.max_steps - 1);
+    a.tiles_x = (a.one.nx + w - 1) / w;
+    const int64_t tiles = (int64_t)a.tiles_x * ((a.one.ny + a.tile_rows - 1) / a.tile_rows);
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    a.ntiles = (int32_t)tiles;
+    a.xcd_swizzle = 1;  // adjacent tiles share lines: let them share an L2
+    switch (coll) {
+    case CO_MINXENT4: return launch_d2q9_pipe_0(st, src, dst, a, s);
+    case CO_MINXENT2: return launch_d2q9_pipe_1(st, src, dst, a, s);
+    case CO_SRT: return launch_d2q9_pipe_2(st, src, dst, a, s);
+    case CO_TRT: return launch_d2q9_pipe_3(st, src, dst, a, s);
+    case CO_MRT: return launch_d2q9_pipe_4(st, src, dst, a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+}  // namespace
+
 hipError_t launch_d2q9_step(int st, int coll, int v, const void *src, void *dst, const StepArgs &a, hipStream_t s)
 {
     if (v < 0 || v >= d2q9_variant_count(coll)) return hipErrorInvalidValue;
-    if (d2q9_variant_window(coll, v)) return launch_d2q9_window(st, coll, src, dst, a, s);
+    const int k = shape_of(coll, v);
+    if (k >= kFirstPipe && a.max_steps > 1) return launch_d2q9_pipe(st, coll, src, dst, a, s);
+    if (k >= kFirstPipe) v = 0;  // one step
+    else if (k >= kFirstWindow) return launch_d2q9_window(st, coll, src, dst, a, s);
     switch (st) {
     case ST_F64: return dispatch9c<ST_F64>(coll, v, src, dst, a, s);
     case ST_F32N64: return dispatch9c<ST_F32N64>(coll, v, src, dst, a, s);

@@ -55,6 +55,7 @@ struct StepArgs {
     int32_t bc;
     int32_t ntiles;
     int32_t tiles_x;        // single D2Q9: tiles along x
+    int32_t tile_rows;      // register pipeline: rows of a tile
     int32_t xcd_swizzle;
     float fp16_scale;       // FP16DEV: 2^k
     float fp16_iscale;      // 2^-k
@@ -73,8 +74,8 @@ const char *d2q9_variant_name(int coll, int variant);
 int d2q9_variant_steps(int coll, int variant);
 bool d2q9_variant_window(int coll, int variant);
 // Shape a single lattice runs in unless another is set: the fastest by the
-// estimates above its definition, among shape 0 and the window shapes (none
-// of which needs set-up).
+// estimates above its definition, among shape 0, the window shapes and the
+// register pipelines (none of which needs set-up).
 int d2q9_default_variant(int storage, int coll, int nx, int ny, int bc);
 hipError_t prepare_d2q9_variant(int st, int coll, int variant);
 hipError_t launch_d2q9_step(int storage, int coll, int variant, const void *src, void *dst,
@@ -90,6 +91,18 @@ int d2q9_window_cap(int storage);
 bool d2q9_window_plan(int storage, int coll, int nx, int ny, int bc, int k, WindowTile *tile,
                       double *us_per_step);
 hipError_t launch_d2q9_window(int storage, int coll, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+// Register-pipeline shapes (pipeline.hip): whether a shape is one; the tile
+// rows for launches of k steps of one lattice, with the estimated
+// microseconds per step; and one launcher per collision rule for
+// a.max_steps steps (2 to 4) with tiles of a.tile_rows rows.
+bool d2q9_variant_pipe(int coll, int variant);
+int d2q9_variant_rows(int coll, int variant);  // fixed tile rows of such a shape, or 0: d2q9_pipe_rows
+int d2q9_pipe_rows(int storage, int coll, int nx, int ny, int k, double *us_per_step);
+hipError_t launch_d2q9_pipe_0(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+hipError_t launch_d2q9_pipe_1(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+hipError_t launch_d2q9_pipe_2(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+hipError_t launch_d2q9_pipe_3(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+hipError_t launch_d2q9_pipe_4(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
 int d1q3_variant_count();
 const char *d1q3_variant_name(int variant);
 int d1q3_variant_steps(int variant);  // steps one launch takes at most (K-step shapes; StepArgs::max_steps sets fewer)

@@ -163,6 +163,7 @@ struct lbm_ctx {
     int variant = 0;
     int spl = 1;             // steps one launch of the current shape takes at most
     lbm::WindowTile win{};   // tile of the current shape if it is an on-chip window shape
+    int tile_rows = 0;       // tile rows of the current shape if it is a register pipeline
     int graph_chunk = 0;
     int32_t pad = -1;        // plane pad in bytes; -1: the context takes none
     int64_t plane_base = 0;  // plane length before the pad (elements)
@@ -323,6 +324,7 @@ lbm::StepArgs step_args(const lbm_ctx *c, DevStatus *status, int64_t step, const
     a.fp16_iscale = c->iscale;
     a.max_steps = 2;  // launchers of multi-step shapes set the count they need
     a.win = c->win;
+    a.tile_rows = c->tile_rows;
     return a;
 }
 
@@ -351,8 +353,18 @@ int window_plan(const lbm_params_t &p, int v, lbm::WindowTile *tile)
     return 1;
 }
 
+// Tile rows of register-pipeline shape v for a lattice.
+int pipe_rows(const lbm_params_t &p, int v)
+{
+    const int rows = lbm::d2q9_variant_rows(p.collision, v);
+    return rows ? rows
+                : lbm::d2q9_pipe_rows(storage_of(p.precision), p.collision, p.nx, p.ny,
+                                      lbm::d2q9_variant_steps(p.collision, v), nullptr);
+}
+
 // Steps one launch of shape v takes at most: 2 for the temporally blocked
-// D2Q9 shapes, what fits for the on-chip window shapes, up to 256 for the
+// D2Q9 shapes, 2 to 4 for the register pipelines, what fits for the on-chip
+// window shapes, up to 256 for the
 // K-step D1Q3 shapes, else 1.
 int launch_steps(const lbm_ctx *c, int v)
 {
@@ -372,7 +384,10 @@ void use_variant(lbm_ctx *c, int v)
     c->variant = -1;  // so that launch_steps() plans anew
     c->win = lbm::WindowTile{};
     c->spl = launch_steps(c, v);
-    if (!c->batch && c->b == 9 && lbm::d2q9_variant_window(c->p.collision, v)) window_plan(c->p, v, &c->win);
+    if (!c->batch && c->b == 9) {
+        if (lbm::d2q9_variant_window(c->p.collision, v)) window_plan(c->p, v, &c->win);
+        if (lbm::d2q9_variant_pipe(c->p.collision, v)) c->tile_rows = pipe_rows(c->p, v);
+    }
     c->variant = v;
 }
 
@@ -1094,7 +1109,12 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
     // The shape a context would start with: none of those needs set-up or
     // memory, so all of them run here and under capture.
     const int v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc) : 0;
-    const int spl = b == 9 && lbm::d2q9_variant_window(p->collision, v) ? window_plan(*p, v, &a.win) : 1;
+    int spl = 1;
+    if (b == 9) {
+        spl = lbm::d2q9_variant_window(p->collision, v) ? window_plan(*p, v, &a.win)
+                                                        : lbm::d2q9_variant_steps(p->collision, v);
+        if (lbm::d2q9_variant_pipe(p->collision, v)) a.tile_rows = pipe_rows(*p, v);
+    }
     int cur = 0;
     for (int64_t i = 0; i < nsteps;) {
         a.step = i;
