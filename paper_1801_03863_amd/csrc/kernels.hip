@@ -924,39 +924,71 @@ __global__ __launch_bounds__(BLK) void k_d1q3_batch(const typename Form<ST>::T *
 // State set-up and read-back (off the hot loop; FP64 in and out).
 // --------------------------------------------------------------------------
 
-// Storage node (x, y) receives, for each direction a, the value that node
-// (x, y) + v_a must pull at the next step: the equilibrium of that node's
-// fields (or the given populations).  Destinations outside the lattice take
-// the node's own value.
+// Node of a range of consecutive global node numbers (the instances' nodes one
+// after another): its instance and its number there.  The range of instances
+// a block meets is found once for the block (scalar), so most lanes have
+// nothing left to search.
+__device__ __forceinline__ int find_instance(const int64_t *__restrict__ prefix, int lo, int hi, int64_t g)
+{
+    while (lo < hi) {  // the last i in [lo, hi] with prefix[i] <= g
+        const int mid = (lo + hi + 1) >> 1;
+        if (prefix[mid] <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+struct RangeNode {
+    int inst;
+    int node;
+};
+
+__device__ __forceinline__ RangeNode range_node(const NodeRange &r, int64_t g)
+{
+    if (!r.inst) return {0, (int)g};
+    const int64_t b0 = r.g0 + (int64_t)blockIdx.x * 256;
+    const int64_t b1 = b0 + 255 < r.g1 ? b0 + 255 : r.g1 - 1;
+    const int lo = find_instance(r.prefix, 0, r.n - 1, b0);
+    const int i = find_instance(r.prefix, lo, find_instance(r.prefix, lo, r.n - 1, b1), g);
+    return {i, (int)(g - r.prefix[i])};
+}
+
+// State set-up from the fields (or populations: b planes per instance) of
+// nodes [g0, g1).  Storage slot (a, s) keeps what node s + v_a pulls next: node
+// j therefore writes its own value of direction a to the slot of j - v_a, and
+// to its own slot where j + v_a lies outside the lattice.  Every slot is
+// written once and every field read once.
 template <int ST, int B>
-__global__ void k_init(Inst in, int bc, const double *__restrict__ rho, const double *__restrict__ ux,
-                       const double *__restrict__ uy, const double *__restrict__ fin, typename Form<ST>::T *buf,
-                       float scale)
+__global__ __launch_bounds__(256) void k_init(NodeRange range, const double *__restrict__ rho,
+                                              const double *__restrict__ ux, const double *__restrict__ uy,
+                                              const double *__restrict__ fin, typename Form<ST>::T *buf,
+                                              float scale)
 {
     using C = typename Form<ST>::C;
-    const int nx = in.nx, ny = in.ny;
-    const int n = nx * ny;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = i % nx, y = i / nx;
+    const int64_t g = range.g0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= range.g1) return;
+    const RangeNode rn = range_node(range, g);
+    const Inst &in = range.inst ? range.inst[rn.inst] : range.one;
+    const int64_t i = g - range.g0;  // of the field arrays
+    const int nx = in.nx, ny = in.ny, bc = range.bc;
+    const int j = rn.node;
+    const double *fi = fin ? fin + B * (g - j) : nullptr;
+    const int x = j % nx, y = j / nx;
     const bool xw = bc == BC_PERIODIC;
     const bool yw = (bc == BC_PERIODIC || bc == BC_TUBE) && B == 9;
     typename Form<ST>::T *d = buf + in.offset;
+    const bool lid = B == 9 && bc == BC_CAVITY && y == ny - 1;
+    const double r = fin || lid ? 0.0 : rho[i], u = fin || lid ? 0.0 : ux[i];
+    const double w = fin || lid || B != 9 ? 0.0 : uy[i];
     for (int a = 0; a < B; ++a) {
         const int vx = (B == 9) ? cx9(a) : (a == 1 ? 1 : (a == 2 ? -1 : 0));
         const int vy = (B == 9) ? cy9(a) : 0;
-        int tx = x + vx, ty = y + vy;
-        if (tx < 0 || tx >= nx) tx = xw ? (tx + nx) % nx : x;
-        if (ty < 0 || ty >= ny) ty = yw ? (ty + ny) % ny : y;
-        if ((tx == x && vx != 0 && !xw) || (ty == y && vy != 0 && !yw)) { tx = x; ty = y; }
-        const int j = ty * nx + tx;
         double v;
         if (fin) {
-            v = fin[(int64_t)a * n + j];
-        } else if (B == 9 && bc == BC_CAVITY && ty == ny - 1) {
+            v = fi[(int64_t)a * nx * ny + j];
+        } else if (lid) {
             v = in.lid[a];
         } else {
-            const double r = rho[j], u = ux[j], w = (B == 9) ? uy[j] : 0.0;
             const double cu = vx * u + vy * w;
             const double wa = (B == 9) ? ((a == 0) ? 4.0 / 9.0 : (a < 5 ? 1.0 / 9.0 : 1.0 / 36.0))
                                        : (a == 0 ? 2.0 / 3.0 : 1.0 / 6.0);
@@ -968,29 +1000,42 @@ __global__ void k_init(Inst in, int bc, const double *__restrict__ rho, const do
         } else {
             ref = (a == 0 ? C(2.0 / 3.0) : C(1.0 / 6.0)) * C(in.rho0);
         }
-        store<ST>(d + (int64_t)a * in.plane + (int64_t)y * in.pitch + x, C(v), ref, scale);
+        typename Form<ST>::T *p = d + (int64_t)a * in.plane;
+        int sx = x - vx, sy = y - vy;  // the node this one pulls direction a from
+        if (xw) sx = sx < 0 ? sx + nx : (sx >= nx ? sx - nx : sx);
+        if (yw) sy = sy < 0 ? sy + ny : (sy >= ny ? sy - ny : sy);
+        if (sx >= 0 && sx < nx && sy >= 0 && sy < ny) store<ST>(p + (int64_t)sy * in.pitch + sx, C(v), ref, scale);
+        const int tx = x + vx, ty = y + vy;
+        const bool out = (!xw && (tx < 0 || tx >= nx)) || (!yw && (ty < 0 || ty >= ny));
+        if (out) store<ST>(p + (int64_t)y * in.pitch + x, C(v), ref, scale);
     }
 }
 
+// Moments or populations of nodes [g0, g1), written from the first element of
+// the output arrays on (device memory, or host memory the device can write:
+// 55 GB/s over the link, the rate of its copy engines).
 template <int ST, int B>
-__global__ void k_gather(Inst in, int bc, const typename Form<ST>::T *__restrict__ buf, double *rho, double *ux,
-                         double *uy, double *fout, float iscale)
+__global__ __launch_bounds__(256) void k_gather(NodeRange range, const typename Form<ST>::T *__restrict__ buf,
+                                                double *rho, double *ux, double *uy, double *fout, int64_t fstride,
+                                                float iscale)
 {
     using C = typename Form<ST>::C;
-    const int nx = in.nx, ny = in.ny;
-    const int n = nx * ny;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int x = i % nx, y = i / nx;
+    const int64_t g = range.g0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= range.g1) return;
+    const RangeNode rn = range_node(range, g);
+    const Inst &in = range.inst ? range.inst[rn.inst] : range.one;
+    const int64_t i = g - range.g0;  // of the output arrays
+    const int nx = in.nx, ny = in.ny, bc = range.bc;
+    const int x = rn.node % nx, y = rn.node / nx;
     const int pitch = in.pitch;
     const typename Form<ST>::T *s = buf + in.offset;
     double f[9];
     if (B == 9) {
         C ref[9];
         ref9<C>(C(in.rho0), ref);
-        C g[9];
-        pull9<ST>(s, in.plane, x, y, pitch, neighbours(x, y, nx, ny, bc), ref, iscale, g);
-        for (int a = 0; a < 9; ++a) f[a] = double(g[a]);
+        C h[9];
+        pull9<ST>(s, in.plane, x, y, pitch, neighbours(x, y, nx, ny, bc), ref, iscale, h);
+        for (int a = 0; a < 9; ++a) f[a] = double(h[a]);
     } else {
         const bool wrap = bc == BC_PERIODIC;
         const int xm = x > 0 ? x - 1 : (wrap ? nx - 1 : 0);
@@ -1001,7 +1046,7 @@ __global__ void k_gather(Inst in, int bc, const typename Form<ST>::T *__restrict
         f[2] = double(load<ST>(s + 2 * in.plane + xp, r1, iscale));
     }
     if (fout) {
-        for (int a = 0; a < B; ++a) fout[(int64_t)a * n + i] = f[a];
+        for (int a = 0; a < B; ++a) fout[a * fstride + i] = f[a];
         return;
     }
     double r, jx, jy;
@@ -1731,30 +1776,30 @@ hipError_t dispatch3b(int v, const void *src, void *dst, const StepArgs &a_in, h
 }
 
 template <int ST>
-hipError_t init_st(int lattice, const Inst &in, int bc, const double *r, const double *u, const double *w,
+hipError_t init_st(int lattice, const NodeRange &r, const double *rho, const double *ux, const double *uy,
                    const double *f, void *buf, float scale, hipStream_t s)
 {
     using T = typename Form<ST>::T;
-    const int n = in.nx * in.ny;
-    const int blocks = (n + 255) / 256;
+    const unsigned blocks = (unsigned)((r.g1 - r.g0 + 255) / 256);
     if (lattice == 9)
-        hipLaunchKernelGGL((k_init<ST, 9>), dim3(blocks), dim3(256), 0, s, in, bc, r, u, w, f, (T *)buf, scale);
+        hipLaunchKernelGGL((k_init<ST, 9>), dim3(blocks), dim3(256), 0, s, r, rho, ux, uy, f, (T *)buf, scale);
     else
-        hipLaunchKernelGGL((k_init<ST, 3>), dim3(blocks), dim3(256), 0, s, in, bc, r, u, w, f, (T *)buf, scale);
+        hipLaunchKernelGGL((k_init<ST, 3>), dim3(blocks), dim3(256), 0, s, r, rho, ux, uy, f, (T *)buf, scale);
     return hipGetLastError();
 }
 
 template <int ST>
-hipError_t gather_st(int lattice, const Inst &in, int bc, const void *buf, double *r, double *u, double *w,
-                     double *f, float iscale, hipStream_t s)
+hipError_t gather_st(int lattice, const NodeRange &r, const void *buf, double *rho, double *ux, double *uy,
+                     double *f, int64_t fstride, float iscale, hipStream_t s)
 {
     using T = typename Form<ST>::T;
-    const int n = in.nx * in.ny;
-    const int blocks = (n + 255) / 256;
+    const unsigned blocks = (unsigned)((r.g1 - r.g0 + 255) / 256);
     if (lattice == 9)
-        hipLaunchKernelGGL((k_gather<ST, 9>), dim3(blocks), dim3(256), 0, s, in, bc, (const T *)buf, r, u, w, f, iscale);
+        hipLaunchKernelGGL((k_gather<ST, 9>), dim3(blocks), dim3(256), 0, s, r, (const T *)buf, rho, ux, uy, f, fstride,
+                           iscale);
     else
-        hipLaunchKernelGGL((k_gather<ST, 3>), dim3(blocks), dim3(256), 0, s, in, bc, (const T *)buf, r, u, w, f, iscale);
+        hipLaunchKernelGGL((k_gather<ST, 3>), dim3(blocks), dim3(256), 0, s, r, (const T *)buf, rho, ux, uy, f, fstride,
+                           iscale);
     return hipGetLastError();
 }
 
@@ -2034,26 +2079,28 @@ hipError_t launch_d1q3_batch_step(int st, int v, const void *src, void *dst, con
     }
 }
 
-hipError_t launch_init(int lattice, int st, const Inst &in, int bc, const double *r, const double *u,
-                       const double *w, const double *f, void *buf, float scale, hipStream_t s)
+hipError_t launch_init(int lattice, int st, const NodeRange &r, const double *rho, const double *ux, const double *uy,
+                       const double *f, void *buf, float scale, hipStream_t s)
 {
+    if (r.g1 <= r.g0) return hipSuccess;
     switch (st) {
-    case ST_F64: return init_st<ST_F64>(lattice, in, bc, r, u, w, f, buf, scale, s);
-    case ST_F32N64: return init_st<ST_F32N64>(lattice, in, bc, r, u, w, f, buf, scale, s);
-    case ST_F32: return init_st<ST_F32>(lattice, in, bc, r, u, w, f, buf, scale, s);
-    case ST_F16DEV: return init_st<ST_F16DEV>(lattice, in, bc, r, u, w, f, buf, scale, s);
+    case ST_F64: return init_st<ST_F64>(lattice, r, rho, ux, uy, f, buf, scale, s);
+    case ST_F32N64: return init_st<ST_F32N64>(lattice, r, rho, ux, uy, f, buf, scale, s);
+    case ST_F32: return init_st<ST_F32>(lattice, r, rho, ux, uy, f, buf, scale, s);
+    case ST_F16DEV: return init_st<ST_F16DEV>(lattice, r, rho, ux, uy, f, buf, scale, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_gather(int lattice, int st, const Inst &in, int bc, const void *buf, double *r, double *u,
-                         double *w, double *f, float iscale, hipStream_t s)
+hipError_t launch_gather(int lattice, int st, const NodeRange &r, const void *buf, double *rho, double *ux, double *uy,
+                         double *f, int64_t fstride, float iscale, hipStream_t s)
 {
+    if (r.g1 <= r.g0) return hipSuccess;
     switch (st) {
-    case ST_F64: return gather_st<ST_F64>(lattice, in, bc, buf, r, u, w, f, iscale, s);
-    case ST_F32N64: return gather_st<ST_F32N64>(lattice, in, bc, buf, r, u, w, f, iscale, s);
-    case ST_F32: return gather_st<ST_F32>(lattice, in, bc, buf, r, u, w, f, iscale, s);
-    case ST_F16DEV: return gather_st<ST_F16DEV>(lattice, in, bc, buf, r, u, w, f, iscale, s);
+    case ST_F64: return gather_st<ST_F64>(lattice, r, buf, rho, ux, uy, f, fstride, iscale, s);
+    case ST_F32N64: return gather_st<ST_F32N64>(lattice, r, buf, rho, ux, uy, f, fstride, iscale, s);
+    case ST_F32: return gather_st<ST_F32>(lattice, r, buf, rho, ux, uy, f, fstride, iscale, s);
+    case ST_F16DEV: return gather_st<ST_F16DEV>(lattice, r, buf, rho, ux, uy, f, fstride, iscale, s);
     default: return hipErrorInvalidValue;
     }
 }

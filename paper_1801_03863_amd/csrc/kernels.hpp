@@ -126,17 +126,26 @@ int batch_tile_nodes(int lattice, int variant);
 const char *batch_variant_name(int lattice, int variant);
 hipError_t prepare_batch_variant(int st, int coll, int variant);
 
-// Set the state of one instance: pre-shifted equilibrium of FP64 fields
-// (d_rho, d_ux, d_uy: nx*ny device doubles) or of FP64 populations (d_f:
-// b planes of nx*ny device doubles).
-hipError_t launch_init(int lattice, int storage, const Inst &in, int bc, const double *d_rho,
-                       const double *d_ux, const double *d_uy, const double *d_f, void *buf,
-                       float fp16_scale, hipStream_t s);
-// Gather the pre-collision populations of one instance and write either its
-// moments (d_rho, d_ux, d_uy) or the populations (d_f), as doubles.
-hipError_t launch_gather(int lattice, int storage, const Inst &in, int bc, const void *buf,
-                         double *d_rho, double *d_ux, double *d_uy, double *d_f, float fp16_iscale,
-                         hipStream_t s);
+// Nodes [g0, g1) of all instances counted one after another.
+struct NodeRange {
+    const Inst *inst;       // device table, or nullptr: `one`
+    const int64_t *prefix;  // device: number of the first node of each instance
+    Inst one;
+    int32_t n, bc;
+    int64_t g0, g1;
+};
+
+// Set the state of a range of nodes: pre-shifted equilibrium of FP64 fields
+// (node g is element g - g0 of each), or FP64 populations f (of all nodes: b
+// planes per instance).
+hipError_t launch_init(int lattice, int storage, const NodeRange &r, const double *rho, const double *ux,
+                       const double *uy, const double *f, void *buf, float fp16_scale, hipStream_t s);
+// Gather the pre-collision populations of a range of nodes and write either
+// their moments (any of rho, ux, uy may be null) or the populations (f: planes
+// fstride apart), as doubles.  Node g is element g - g0 of every array, in
+// device memory or host memory the device can write.
+hipError_t launch_gather(int lattice, int storage, const NodeRange &r, const void *buf, double *rho, double *ux,
+                         double *uy, double *f, int64_t fstride, float fp16_iscale, hipStream_t s);
 
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s);
 hipError_t launch_add_step_base(int64_t *base, int64_t n, hipStream_t s);

@@ -5,11 +5,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/lbm.h"
@@ -60,6 +63,18 @@ constexpr int64_t kMaxBatchNodes = int64_t(1) << 22;
 // the fewest lines, and row writes fill whole lines.  Lattices of arbitrary
 // width (a batch's instances) would otherwise start most rows mid-line.
 constexpr int64_t kRowLineBytes = 128;
+
+// Fields and populations are read back through pinned slots of this size that
+// kernels write directly; when there are several, up to kCopyThreads host
+// threads copy them to the caller's arrays.  One thread fills fresh pages at
+// 16 GB/s, two at 28, four at 49, eight at 72; the link carries 55 GB/s; the
+// runtime's own copy to pageable memory 8 to 10 GB/s (2048^2 moments, 100 MB:
+// 10.5 -> 3.3 ms).  Uploads stay with the runtime's copies, which reach 30 GB/s
+// (100 MB: 3.5 ms, against 5.0 through the slots).
+constexpr size_t kSlotBytes = 1536 << 10;
+constexpr size_t kMinSlotBytes = 128 << 10;  // smaller pinned blocks take longer to allocate (0.3 ms against 20 us)
+constexpr int kSlots = 12;
+constexpr int kCopyThreads = 8;
 
 size_t elem_bytes(int precision)
 {
@@ -140,7 +155,8 @@ struct lbm_ctx {
     int n = 1;
     std::vector<Inst> inst;
     std::vector<int64_t> node_prefix;  // host offsets of each instance's fields
-    Inst *d_inst = nullptr;
+    Inst *d_inst = nullptr;      // batched: instance table, and behind it
+    int64_t *d_prefix = nullptr; // node_prefix on the device (same allocation)
     int32_t *d_tile_inst = nullptr;
     int32_t *d_tile_first = nullptr;
     int ntiles = 0;
@@ -452,6 +468,60 @@ int capture_graph(lbm_ctx *c, int parity)
     return LBM_OK;
 }
 
+// Pinned slots of a read-back.  One set (at most kSlots * kSlotBytes) serves
+// every context of the process, so that a new context's first read-back does
+// not wait for a pinned allocation (up to 2 ms); it is given back when the last
+// context goes.  A read-back that finds it in use by another thread takes a set
+// of its own for the call.
+struct Stage {
+    char *mem = nullptr;
+    size_t slot_bytes = 0;
+    int slots = 0;
+
+    void drop()
+    {
+        if (mem) (void)hipHostFree(mem);
+        mem = nullptr;
+        slot_bytes = 0;
+        slots = 0;
+    }
+
+    // Slots for `bytes` in all, or those that are there if they are enough.
+    int ready(size_t bytes)
+    {
+        const size_t slot = bytes <= kSlotBytes ? std::max(kMinSlotBytes, (bytes + 4095) / 4096 * 4096) : kSlotBytes;
+        const int want = (int)std::min<size_t>(kSlots, (bytes + slot - 1) / slot);
+        if (slot_bytes >= slot && slots >= want) return LBM_OK;
+        drop();
+        if (hipHostMalloc((void **)&mem, slot * want, hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
+            mem = nullptr;
+            return fail(LBM_ENOMEM, "hipHostMalloc of %s failed", "the read-back slots");
+        }
+        slot_bytes = slot;
+        slots = want;
+        return LBM_OK;
+    }
+};
+
+std::mutex g_stage_mu;    // held by the read-back that uses g_stage
+Stage g_stage;
+std::mutex g_users_mu;
+int g_users = 0;          // contexts alive
+
+void add_user()
+{
+    std::lock_guard<std::mutex> l(g_users_mu);
+    ++g_users;
+}
+
+void drop_user()
+{
+    std::lock_guard<std::mutex> l(g_users_mu);
+    if (--g_users > 0) return;
+    std::lock_guard<std::mutex> s(g_stage_mu);
+    g_stage.drop();
+}
+
 void destroy(lbm_ctx *c)
 {
     if (!c) return;
@@ -460,13 +530,12 @@ void destroy(lbm_ctx *c)
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->own_ws && c->ws) (void)hipFree(c->ws);
-    if (c->d_status) (void)hipFree(c->d_status);
-    if (c->d_status_scratch) (void)hipFree(c->d_status_scratch);
-    if (c->d_step_base) (void)hipFree(c->d_step_base);
-    if (c->d_inst) (void)hipFree(c->d_inst);
+    if (c->d_status) (void)hipFree(c->d_status);  // and the scratch records and step base behind it
+    if (c->d_inst) (void)hipFree(c->d_inst);      // and the node numbers behind it
     if (c->d_tile_inst) (void)hipFree(c->d_tile_inst);
     if (c->d_tile_first) (void)hipFree(c->d_tile_first);
     delete c;
+    drop_user();
 }
 
 int check_device(std::string *arch)
@@ -483,39 +552,213 @@ int check_device(std::string *arch)
     return LBM_OK;
 }
 
+// --------------------------------------------------------------------------
+// State upload and read-back
+// --------------------------------------------------------------------------
+
+// Read all nodes back in pieces of `piece` nodes through the slots:
+// launch(g0, g1, slot) enqueues the kernel that fills a slot, copy(g0, g1,
+// slot) empties it into the caller's arrays once that kernel has ended, and
+// the slot's next piece waits for that.  Returns with every copy ended.
+template <class Launch, class Copy>
+int read_pieces(lbm_ctx *c, const Stage &stage, int64_t piece, Launch launch, Copy copy)
+{
+    const int64_t total = c->nodes, n = (total + piece - 1) / piece;
+    const int S = (int)std::min<int64_t>(stage.slots, n);
+    struct Events {
+        hipEvent_t e[kSlots] = {};
+        ~Events()
+        {
+            for (hipEvent_t x : e)
+                if (x) (void)hipEventDestroy(x);
+        }
+    } ev;
+    for (int k = 0; k < S; ++k) HIPCHK(hipEventCreateWithFlags(&ev.e[k], hipEventDisableTiming));
+    auto slot = [&](int64_t k) { return (double *)(stage.mem + (size_t)(k % S) * stage.slot_bytes); };
+    auto lo = [&](int64_t k) { return k * piece; };
+    auto hi = [&](int64_t k) { return std::min(total, (k + 1) * piece); };
+    auto enqueue = [&](int64_t k) {
+        hipError_t e = launch(lo(k), hi(k), slot(k));
+        return e == hipSuccess ? hipEventRecord(ev.e[k % S], c->stream) : e;
+    };
+    auto finish = [&](hipError_t e) {
+        const hipError_t e2 = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) e = e2;
+        return e == hipSuccess ? LBM_OK : hip_fail(e, "state read-back");
+    };
+    auto drain = [&](int64_t k) {
+        const hipError_t e = hipEventSynchronize(ev.e[k % S]);
+        if (e == hipSuccess) copy(lo(k), hi(k), slot(k));
+        return e;
+    };
+    if (n <= 3 || S < 4) {  // a few pieces: no threads
+        hipError_t e = hipSuccess;
+        for (int64_t k = 0; k < n + S && e == hipSuccess; ++k) {
+            if (k >= S && k - S < n) e = drain(k - S);
+            if (k < n && e == hipSuccess) e = enqueue(k);
+        }
+        return finish(e);
+    }
+    struct Shared {
+        std::mutex mu;
+        std::condition_variable cv;
+        std::vector<char> copied;
+        std::atomic<int64_t> next{0};
+        int64_t launched = 0;
+        hipError_t err = hipSuccess;
+        bool stop = false;
+    } sh;
+    auto stop = [&](hipError_t e) {
+        std::lock_guard<std::mutex> l(sh.mu);
+        if (!sh.stop) sh.err = e;
+        sh.stop = true;
+        sh.cv.notify_all();
+    };
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    auto worker = [&] {
+        hipError_t e = hipSetDevice(dev);
+        for (int64_t k; e == hipSuccess && (k = sh.next.fetch_add(1)) < n;) {
+            {
+                std::unique_lock<std::mutex> l(sh.mu);
+                sh.cv.wait(l, [&] { return sh.stop || sh.launched > k; });
+                if (sh.stop) return;
+            }
+            e = drain(k);
+            std::lock_guard<std::mutex> l(sh.mu);
+            sh.copied[(size_t)k] = 1;
+            sh.cv.notify_all();
+        }
+        if (e != hipSuccess) stop(e);
+    };
+    const int hw = (int)std::thread::hardware_concurrency();
+    const int want = (int)std::min<int64_t>(std::min(kCopyThreads, std::max(1, hw / 2)), n / 2);
+    std::vector<std::thread> threads;
+    try {
+        sh.copied.assign((size_t)n, 0);
+        threads.reserve((size_t)want);
+        for (int i = 0; i < want; ++i) threads.emplace_back(worker);
+    } catch (...) {
+        // fewer threads than asked for: the pieces wait for those there are
+    }
+    if (threads.empty()) return fail(LBM_ENOMEM, "no thread for the host copies");
+    for (int64_t k = 0; k < n; ++k) {
+        if (k >= S) {
+            std::unique_lock<std::mutex> l(sh.mu);
+            sh.cv.wait(l, [&] { return sh.stop || sh.copied[(size_t)(k - S)]; });
+            if (sh.stop) break;
+        }
+        const hipError_t e = enqueue(k);
+        if (e != hipSuccess) {
+            stop(e);
+            break;
+        }
+        std::lock_guard<std::mutex> l(sh.mu);
+        sh.launched = k + 1;
+        sh.cv.notify_all();
+    }
+    for (auto &th : threads) th.join();
+    return finish(sh.err);
+}
+
+// Nodes of a piece for `planes` values per node: whole blocks, unless one slot
+// holds everything.
+int64_t piece_nodes(const lbm_ctx *c, const Stage &stage, int planes)
+{
+    const int64_t fit = (int64_t)(stage.slot_bytes / (8 * (size_t)planes));
+    return fit >= c->nodes ? c->nodes : std::max<int64_t>(256, fit / 256 * 256);
+}
+
+lbm::NodeRange node_range(const lbm_ctx *c, int64_t g0, int64_t g1)
+{
+    lbm::NodeRange r{};
+    r.inst = c->d_inst;
+    r.prefix = c->d_prefix;
+    r.one = c->inst[0];
+    r.n = c->n;
+    r.bc = c->p.bc;
+    r.g0 = g0;
+    r.g1 = g1;
+    return r;
+}
+
+// Copy populations of nodes [g0, g1) from a slot (planes `piece` apart) to the
+// caller's array (b planes per instance).
+void copy_populations(const lbm_ctx *c, int64_t g0, int64_t g1, const double *slot, int64_t piece, double *to)
+{
+    int i = (int)(std::upper_bound(c->node_prefix.begin(), c->node_prefix.end(), g0) - c->node_prefix.begin()) - 1;
+    for (int64_t g = g0; g < g1; ++i) {
+        const int64_t first = c->node_prefix[i], m = (int64_t)c->inst[i].nx * c->inst[i].ny;
+        const int64_t end = std::min(g1, first + m);
+        for (int q = 0; q < c->b; ++q)
+            std::memcpy(to + c->b * first + q * m + (g - first), slot + q * piece + (g - g0),
+                        sizeof(double) * (size_t)(end - g));
+        g = end;
+    }
+}
+
 // Upload the fields (or populations) of every instance and write the
 // pre-shifted state into buf[cur].
 int load_state(lbm_ctx *c, const double *rho, const double *ux, const double *uy, const double *f)
 {
     const int64_t total = c->nodes;
+    const size_t bytes = sizeof(double) * (size_t)total;
     double *d = nullptr;
-    const size_t per = f ? (size_t)c->b : 3;
-    HIPCHK(hipMalloc(&d, sizeof(double) * per * (size_t)total));
-    int rc = LBM_OK;
+    HIPCHK(hipMalloc(&d, bytes * (size_t)(f ? c->b : 3)));
     hipError_t e = hipSuccess;
+    auto up = [&](double *to, const double *from, size_t n) {
+        if (e == hipSuccess) e = hipMemcpyAsync(to, from, n, hipMemcpyHostToDevice, c->stream);
+    };
     if (f) {
-        e = hipMemcpyAsync(d, f, sizeof(double) * per * total, hipMemcpyHostToDevice, c->stream);
+        up(d, f, bytes * (size_t)c->b);
     } else {
-        e = hipMemcpyAsync(d, rho, sizeof(double) * total, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(d + total, ux, sizeof(double) * total, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess && uy && c->b == 9)
-            e = hipMemcpyAsync(d + 2 * total, uy, sizeof(double) * total, hipMemcpyHostToDevice, c->stream);
-        else if (e == hipSuccess)
-            e = hipMemsetAsync(d + 2 * total, 0, sizeof(double) * total, c->stream);
+        up(d, rho, bytes);
+        up(d + total, ux, bytes);
+        if (c->b == 9) up(d + 2 * total, uy, bytes);
     }
-    for (int i = 0; i < c->n && e == hipSuccess; ++i) {
-        const int64_t o = c->node_prefix[i];
-        if (f)
-            e = lbm::launch_init(c->b, c->storage, c->inst[i], c->p.bc, nullptr, nullptr, nullptr, d + per * o,
-                                 c->buf[c->cur], c->scale, c->stream);
-        else
-            e = lbm::launch_init(c->b, c->storage, c->inst[i], c->p.bc, d + o, d + total + o, d + 2 * total + o,
-                                 nullptr, c->buf[c->cur], c->scale, c->stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) rc = hip_fail(e, "state upload");
+    if (e == hipSuccess)
+        e = lbm::launch_init(c->b, c->storage, node_range(c, 0, total), d, d + total, d + 2 * total, f ? d : nullptr,
+                             c->buf[c->cur], c->scale, c->stream);
+    const hipError_t e2 = hipStreamSynchronize(c->stream);
     (void)hipFree(d);
-    return rc;
+    if (e == hipSuccess) e = e2;
+    return e == hipSuccess ? LBM_OK : hip_fail(e, "state upload");
+}
+
+// Read the state back as moments (any of rho, ux, uy may be null) or
+// populations.
+int read_state(lbm_ctx *c, double *rho, double *ux, double *uy, double *f)
+{
+    const int planes = f ? c->b : 3;
+    std::unique_lock<std::mutex> shared(g_stage_mu, std::try_to_lock);
+    struct Own : Stage {
+        ~Own() { drop(); }
+    } own;
+    Stage &stage = shared.owns_lock() ? g_stage : own;
+    int rc = stage.ready(sizeof(double) * (size_t)planes * (size_t)c->nodes);
+    if (rc) return rc;
+    const int64_t piece = piece_nodes(c, stage, planes);
+    const void *buf = c->buf[c->cur];
+    if (f)
+        return read_pieces(
+            c, stage, piece,
+            [&](int64_t g0, int64_t g1, double *s) {
+                return lbm::launch_gather(c->b, c->storage, node_range(c, g0, g1), buf, nullptr, nullptr, nullptr, s,
+                                          piece, c->iscale, c->stream);
+            },
+            [&](int64_t g0, int64_t g1, double *s) { copy_populations(c, g0, g1, s, piece, f); });
+    double *to[3] = {rho, ux, uy};
+    return read_pieces(
+        c, stage, piece,
+        [&](int64_t g0, int64_t g1, double *s) {
+            return lbm::launch_gather(c->b, c->storage, node_range(c, g0, g1), buf, rho ? s : nullptr,
+                                      ux ? s + piece : nullptr, uy ? s + 2 * piece : nullptr, nullptr, 0, c->iscale,
+                                      c->stream);
+        },
+        [&](int64_t g0, int64_t g1, double *s) {
+            for (int q = 0; q < 3; ++q)
+                if (to[q]) std::memcpy(to[q] + g0, s + q * piece, sizeof(double) * (size_t)(g1 - g0));
+        });
 }
 
 int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const double *ux, const double *uy,
@@ -529,6 +772,7 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
     int rc = check_device(&arch);
     if (rc) return rc;
     lbm_ctx *c = new lbm_ctx();
+    add_user();
     c->p = p[0];
     c->arch = arch;
     c->b = p[0].lattice == LBM_D1Q3 ? 3 : 9;
@@ -582,9 +826,10 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
             return r_;                             \
         }                                          \
     } while (0)
-    CK(hipMalloc(&c->d_status, sizeof(DevStatus) * n));
-    CK(hipMalloc(&c->d_status_scratch, sizeof(DevStatus) * n));
-    CK(hipMalloc(&c->d_step_base, sizeof(int64_t)));
+    // Status records, the tuner's, and the step base of graphs in one piece.
+    CK(hipMalloc(&c->d_status, sizeof(DevStatus) * 2 * (size_t)n + sizeof(int64_t)));
+    c->d_status_scratch = c->d_status + n;
+    c->d_step_base = (int64_t *)(c->d_status + 2 * (size_t)n);
     if (batch && c->b == 9) {
         int64_t maxn = 0;
         for (int i = 0; i < n; ++i) maxn = std::max<int64_t>(maxn, (int64_t)c->inst[i].nx * c->inst[i].ny);
@@ -599,8 +844,14 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
         }
     }
     if (batch) {
-        CK(hipMalloc(&c->d_inst, sizeof(Inst) * n));
-        CK(hipMemcpy(c->d_inst, c->inst.data(), sizeof(Inst) * n, hipMemcpyHostToDevice));
+        static_assert(sizeof(Inst) % sizeof(int64_t) == 0, "node numbers follow the instance table");
+        const size_t table = sizeof(Inst) * (size_t)n, numbers = sizeof(int64_t) * (size_t)n;
+        std::vector<char> both(table + numbers);
+        std::memcpy(both.data(), c->inst.data(), table);
+        std::memcpy(both.data() + table, c->node_prefix.data(), numbers);
+        CK(hipMalloc(&c->d_inst, table + numbers));
+        c->d_prefix = (int64_t *)((char *)c->d_inst + table);
+        CK(hipMemcpy(c->d_inst, both.data(), table + numbers, hipMemcpyHostToDevice));
         rc = build_tiles(c, lbm::batch_tile_nodes(c->b, 0));
         if (rc) {
             destroy(c);
@@ -609,9 +860,7 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
     }
     if (!batch && c->b == 9)
         use_variant(c, lbm::d2q9_default_variant(c->storage, c->p.collision, c->p.nx, c->p.ny, c->p.bc));
-    CK(lbm::launch_clear_status(c->d_status, n, c->stream));
-    CK(lbm::launch_clear_status(c->d_status_scratch, n, c->stream));
-    CK(lbm::launch_set_step_base(c->d_step_base, 0, c->stream));
+    CK(lbm::launch_clear_status(c->d_status, 2 * n, c->stream));  // the step base is set before a graph reads it
 #undef CK
     rc = load_state(c, rho, ux, uy, nullptr);
     if (rc) {
@@ -960,40 +1209,13 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
 int lbm_moments(lbm_ctx_t *c, double *rho, double *ux, double *uy)
 {
     if (!c) return fail(LBM_EINVAL, "null context");
-    const int64_t total = c->nodes;
-    double *d = nullptr;
-    HIPCHK(hipMalloc(&d, sizeof(double) * 3 * (size_t)total));
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < c->n && e == hipSuccess; ++i) {
-        const int64_t o = c->node_prefix[i];
-        e = lbm::launch_gather(c->b, c->storage, c->inst[i], c->p.bc, c->buf[c->cur], d + o, d + total + o,
-                               d + 2 * total + o, nullptr, c->iscale, c->stream);
-    }
-    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, d, sizeof(double) * total, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && ux) e = hipMemcpyAsync(ux, d + total, sizeof(double) * total, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && uy)
-        e = hipMemcpyAsync(uy, d + 2 * total, sizeof(double) * total, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d);
-    if (e != hipSuccess) return hip_fail(e, "lbm_moments");
-    return LBM_OK;
+    return read_state(c, rho, ux, uy, nullptr);
 }
 
 int lbm_get_populations(lbm_ctx_t *c, double *f)
 {
     if (!c || !f) return fail(LBM_EINVAL, "null argument");
-    const size_t count = (size_t)c->b * (size_t)c->nodes;
-    double *d = nullptr;
-    HIPCHK(hipMalloc(&d, sizeof(double) * count));
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < c->n && e == hipSuccess; ++i)
-        e = lbm::launch_gather(c->b, c->storage, c->inst[i], c->p.bc, c->buf[c->cur], nullptr, nullptr, nullptr,
-                               d + (size_t)c->b * c->node_prefix[i], c->iscale, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(f, d, sizeof(double) * count, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d);
-    if (e != hipSuccess) return hip_fail(e, "lbm_get_populations");
-    return LBM_OK;
+    return read_state(c, nullptr, nullptr, nullptr, f);
 }
 
 int lbm_set_populations(lbm_ctx_t *c, const double *f)
@@ -1097,7 +1319,12 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
     // cleared by a kernel (no memset node under graph capture) and the
     // initial state overwrites the first buffer.
     HIPCHK(lbm::launch_clear_status(st, 1, s));
-    HIPCHK(lbm::launch_init(b, storage, inst[0], p->bc, rho, ux, b == 9 ? uy : nullptr, nullptr, buf[0], scale, s));
+    lbm::NodeRange all{};
+    all.one = inst[0];
+    all.n = 1;
+    all.bc = p->bc;
+    all.g1 = nodes;
+    HIPCHK(lbm::launch_init(b, storage, all, rho, ux, b == 9 ? uy : nullptr, nullptr, buf[0], scale, s));
     lbm::StepArgs a{};
     a.inst = nullptr;
     a.one = inst[0];
@@ -1125,8 +1352,8 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
         cur ^= 1;
         i += a.max_steps;
     }
-    HIPCHK(lbm::launch_gather(b, storage, inst[0], p->bc, buf[cur], rho_out, ux_out, b == 9 ? uy_out : nullptr,
-                              nullptr, iscale, s));
+    HIPCHK(lbm::launch_gather(b, storage, all, buf[cur], rho_out, ux_out, b == 9 ? uy_out : nullptr, nullptr, 0, iscale,
+                              s));
     if (status) {
         DevStatus h{};
         HIPCHK(hipMemcpyAsync(&h, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
