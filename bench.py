@@ -47,7 +47,7 @@ SINGLE_STEP_SHAPE = 25
 def kernel_source_digest():
     h = hashlib.sha256()
     for name in ("collide.hpp", "device.hpp", "kernels.hip", "kernels.hpp", "pipeline.hip", "pipeline.hpp",
-                 "window.hip"):
+                 "tube.hip", "window.hip"):
         with open(os.path.join(ROOT, "paper_1801_03863_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

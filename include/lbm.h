@@ -198,10 +198,11 @@ int lbm_set_plane_pad(lbm_ctx_t *ctx, int32_t pad_bytes);
 int lbm_get_layout(const lbm_ctx_t *ctx, int64_t *plane_stride, int32_t *pad_bytes);
 
 /* Force a launch shape by index; LBM_EINVAL if out of range.  Shape 0 takes
- * one step per launch and runs everywhere; a single D2Q9 lattice starts with
+ * one step per launch and runs everywhere.  A single D2Q9 lattice starts with
  * the shape the library estimates to be the fastest without set-up (shape 0,
  * or one that takes several steps per launch: on-chip windows for small and
- * medium lattices, register pipelines beyond), every other context with shape 0.  For a batch, a
+ * medium lattices, register pipelines beyond), a D1Q3 context with one that
+ * keeps the nodes in registers, a D2Q9 batch with shape 0.  For a batch, a
  * shape with another tile size rebuilds the tile tables (a device
  * allocation). */
 int lbm_set_variant(lbm_ctx_t *ctx, int32_t variant);
@@ -216,9 +217,8 @@ const char *lbm_variant_name(const lbm_ctx_t *ctx, int32_t variant);
  * on-chip window shapes (single lattices, every rule; as many as a window
  * holds at the lattice's size); 2, 3 or 4 for the D2Q9 register pipelines
  * (single lattices, every rule), which pass each row from step to step in
- * registers; 16, 32, 64 or 256 for the D1Q3 shapes that keep 1024-node
- * segments on chip for that many steps.
- * HBM then sees one read and one write of every population per launch.
+ * registers; 32 for the D1Q3 shapes that keep the nodes in registers.  HBM
+ * then sees one read and one write of every population per launch.
  * Results are bitwise equal to single steps, status records included;
  * lbm_step() and graph chunks run a remainder as a launch of fewer steps,
  * and a batch instance's step limit can end its steps inside a launch.  0 if

@@ -250,7 +250,8 @@ def lbm_variant_name(ctx, v):
 def lbm_variant_steps(ctx, v):
     """Steps one launch of shape v takes at most (1; 2 for the temporally
     blocked D2Q9 shapes; up to 64 for the D2Q9 on-chip window shapes; 2
-    to 4 for its register pipelines; up to 256 for the D1Q3 shapes that keep segments on chip)."""
+    to 4 for its register pipelines; 32 for the D1Q3 shapes that keep the
+    nodes in registers)."""
     return _lib.lbm_variant_steps(ctx, int(v))
 
 

@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblbm.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 # (object name, source, extra flags): pipeline.hip once per collision rule.
-SOURCES = [("kernels", "kernels.hip", []), ("window", "window.hip", [])]
+SOURCES = [("kernels", "kernels.hip", []), ("window", "window.hip", []), ("tube", "tube.hip", [])]
 SOURCES += [("pipeline%d" % co, "pipeline.hip", ["-DLBM_PIPE_CO=%d" % co]) for co in range(5)]
 SOURCES += [("runtime", "runtime.hip", [])]
 
@@ -42,7 +42,7 @@ def hipcc() -> str:
 # The sources of the device kernels: the launch shapes the autotuner times
 # and caches are defined here, so a cache entry stays valid while they do.
 KERNEL_SOURCES = ["collide.hpp", "device.hpp", "kernels.hip", "kernels.hpp", "pipeline.hip", "pipeline.hpp",
-                  "window.hip"]
+                  "tube.hip", "window.hip"]
 
 
 def source_id() -> str:

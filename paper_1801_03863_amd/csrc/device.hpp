@@ -40,6 +40,15 @@ __device__ __forceinline__ T ldraw(const T *p)
     else return *p;
 }
 
+// Sixteen bytes of stored populations, moved as one vector access.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The same sixteen bytes viewed as elements.
+template <class T>
+struct Chunk {
+    T e[16 / sizeof(T)];
+};
+
 // FP16 deviation of v from ref, scaled by the power of two `scale`: the
 // fused form v*scale - ref*scale rounds once, straight to binary16 (one
 // mixed-precision fma); ref*scale is exact and uniform across the wave.
@@ -542,14 +551,8 @@ __device__ __forceinline__ void lds_wave_sync()
 // --------------------------------------------------------------------------
 
 template <class C>
-__device__ __forceinline__ int node3(C &f0, C &fp, C &fm, int role, C omega)
+__device__ __forceinline__ void collide3(C &f0, C &fp, C &fm, C omega)
 {
-    if (role == R_WALL) {
-        const C t = fp;
-        fp = fm;
-        fm = t;
-        return 0;
-    }
     const C rho = (f0 + fp) + fm;
     const C u = (fp - fm) * rcp(rho);
     const C uu = u * u;
@@ -559,7 +562,46 @@ __device__ __forceinline__ int node3(C &f0, C &fp, C &fm, int role, C omega)
     f0 = f0 + omega * (e0 - f0);
     fp = fp + omega * ((es + eu) - fp);
     fm = fm + omega * ((es - eu) - fm);
+}
+
+template <class C>
+__device__ __forceinline__ int node3(C &f0, C &fp, C &fm, int role, C omega)
+{
+    if (role == R_WALL) {
+        const C t = fp;
+        fp = fm;
+        fm = t;
+        return 0;
+    }
+    collide3(f0, fp, fm, omega);
     return (nonneg_finite(f0) && nonneg_finite(fp) && nonneg_finite(fm)) ? 0 : 1;
+}
+
+// The value of the lane below (left neighbour column) or above; lanes 0 and
+// 63 keep their own, which only dead columns use.
+template <bool FROM_LEFT>
+__device__ __forceinline__ uint32_t wave_shift(uint32_t v)
+{
+    constexpr int ctrl = FROM_LEFT ? 0x138 : 0x130;  // wave_shr:1, wave_shl:1
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false);
+}
+template <bool FROM_LEFT>
+__device__ __forceinline__ float lane_shift(float v)
+{
+    return __builtin_bit_cast(float, wave_shift<FROM_LEFT>(__builtin_bit_cast(uint32_t, v)));
+}
+template <bool FROM_LEFT>
+__device__ __forceinline__ double lane_shift(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = wave_shift<FROM_LEFT>((uint32_t)u), hi = wave_shift<FROM_LEFT>((uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <bool FROM_LEFT>
+__device__ __forceinline__ _Float16 lane_shift(_Float16 v)
+{
+    return __builtin_bit_cast(_Float16,
+                              (uint16_t)wave_shift<FROM_LEFT>((uint32_t)__builtin_bit_cast(uint16_t, v)));
 }
 
 // Wave-level minimum of a 64-bit event key and one atomic for the wave.

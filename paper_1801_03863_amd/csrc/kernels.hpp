@@ -105,12 +105,15 @@ hipError_t launch_d2q9_pipe_3(int storage, const void *src, void *dst, const Ste
 hipError_t launch_d2q9_pipe_4(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
 int d1q3_variant_count();
 const char *d1q3_variant_name(int variant);
-int d1q3_variant_steps(int variant);  // steps one launch takes at most (K-step shapes; StepArgs::max_steps sets fewer)
-hipError_t prepare_d1q3_variant(int st, int batch, int variant);  // host-side set-up before the first launch
+int d1q3_variant_steps(int variant);  // steps one launch takes at most (StepArgs::max_steps sets fewer)
+int d1q3_default_variant(int batch, int64_t nodes);  // shape a context of that many nodes starts in
 hipError_t launch_d1q3_step(int storage, int variant, const void *src, void *dst, const StepArgs &a,
                             hipStream_t s);
 hipError_t launch_d1q3_batch_step(int storage, int variant, const void *src, void *dst,
                                   const StepArgs &a, hipStream_t s);
+// D1Q3 shapes with the nodes in registers (tube.hip), n = 2, 4 or 8 per lane.
+hipError_t launch_d1q3_regs(int storage, int n, int batch, const void *src, void *dst, const StepArgs &a,
+                            hipStream_t s);
 // Batch of small D2Q9 lattices resident in LDS: one workgroup per instance
 // (a.ntiles = instances) runs nsteps steps in one launch; dst receives the
 // final state (it may equal src).

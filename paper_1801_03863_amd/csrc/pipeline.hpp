@@ -36,33 +36,6 @@
 
 namespace lbm {
 
-// The value of the lane below (left neighbour column) or above; lanes 0 and
-// 63 keep their own, which only dead columns use.
-template <bool FROM_LEFT>
-__device__ __forceinline__ uint32_t wave_shift(uint32_t v)
-{
-    constexpr int ctrl = FROM_LEFT ? 0x138 : 0x130;  // wave_shr:1, wave_shl:1
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false);
-}
-template <bool FROM_LEFT>
-__device__ __forceinline__ float lane_shift(float v)
-{
-    return __builtin_bit_cast(float, wave_shift<FROM_LEFT>(__builtin_bit_cast(uint32_t, v)));
-}
-template <bool FROM_LEFT>
-__device__ __forceinline__ double lane_shift(double v)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = wave_shift<FROM_LEFT>((uint32_t)u), hi = wave_shift<FROM_LEFT>((uint32_t)(u >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <bool FROM_LEFT>
-__device__ __forceinline__ _Float16 lane_shift(_Float16 v)
-{
-    return __builtin_bit_cast(_Float16,
-                              (uint16_t)wave_shift<FROM_LEFT>((uint32_t)__builtin_bit_cast(uint16_t, v)));
-}
-
 // What a stage keeps of its output for the next one (after the sideways
 // move): a = row last computed, b = the row before.
 template <class T>

@@ -380,8 +380,7 @@ int pipe_rows(const lbm_params_t &p, int v)
 
 // Steps one launch of shape v takes at most: 2 for the temporally blocked
 // D2Q9 shapes, 2 to 4 for the register pipelines, what fits for the on-chip
-// window shapes, up to 256 for the
-// K-step D1Q3 shapes, else 1.
+// window shapes, 32 for the D1Q3 shapes in registers, else 1.
 int launch_steps(const lbm_ctx *c, int v)
 {
     if (v == c->variant) return c->spl;
@@ -852,14 +851,14 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
         CK(hipMalloc(&c->d_inst, table + numbers));
         c->d_prefix = (int64_t *)((char *)c->d_inst + table);
         CK(hipMemcpy(c->d_inst, both.data(), table + numbers, hipMemcpyHostToDevice));
-        rc = build_tiles(c, lbm::batch_tile_nodes(c->b, 0));
+        rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->b == 3 ? lbm::d1q3_default_variant(1, c->nodes) : 0));
         if (rc) {
             destroy(c);
             return rc;
         }
     }
-    if (!batch && c->b == 9)
-        use_variant(c, lbm::d2q9_default_variant(c->storage, c->p.collision, c->p.nx, c->p.ny, c->p.bc));
+    if (c->b == 3) use_variant(c, lbm::d1q3_default_variant(batch, c->nodes));
+    else if (!batch) use_variant(c, lbm::d2q9_default_variant(c->storage, c->p.collision, c->p.nx, c->p.ny, c->p.bc));
     CK(lbm::launch_clear_status(c->d_status, 2 * n, c->stream));  // the step base is set before a graph reads it
 #undef CK
     rc = load_state(c, rho, ux, uy, nullptr);
@@ -1011,7 +1010,6 @@ int lbm_set_variant(lbm_ctx_t *c, int32_t v)
     if (!c->batch && c->b == 9) HIPCHK(lbm::prepare_d2q9_variant(c->storage, c->p.collision, v));
     if (c->batch && c->b == 9 && v != c->lds_variant)
         HIPCHK(lbm::prepare_batch_variant(c->storage, c->p.collision, v));
-    if (c->b == 3) HIPCHK(lbm::prepare_d1q3_variant(c->storage, c->batch, v));
     use_variant(c, v);
     if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, v) != c->tile_nodes)
         return build_tiles(c, lbm::batch_tile_nodes(c->b, v));
@@ -1335,8 +1333,9 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
     a.fp16_iscale = iscale;
     // The shape a context would start with: none of those needs set-up or
     // memory, so all of them run here and under capture.
-    const int v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc) : 0;
-    int spl = 1;
+    const int v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc)
+                         : lbm::d1q3_default_variant(0, nodes);
+    int spl = b == 9 ? 1 : lbm::d1q3_variant_steps(v);
     if (b == 9) {
         spl = lbm::d2q9_variant_window(p->collision, v) ? window_plan(*p, v, &a.win)
                                                         : lbm::d2q9_variant_steps(p->collision, v);
