@@ -202,9 +202,9 @@ int lbm_get_layout(const lbm_ctx_t *ctx, int64_t *plane_stride, int32_t *pad_byt
  * the shape the library estimates to be the fastest without set-up (shape 0,
  * or one that takes several steps per launch: on-chip windows for small and
  * medium lattices, register pipelines beyond), a D1Q3 context with one that
- * keeps the nodes in registers, a D2Q9 batch with shape 0.  For a batch, a
- * shape with another tile size rebuilds the tile tables (a device
- * allocation). */
+ * keeps the nodes in registers, a D2Q9 batch with a register pipeline or, if
+ * it is small, shape 0.  For a batch, a shape with another tile size rebuilds
+ * the tile tables (a device allocation). */
 int lbm_set_variant(lbm_ctx_t *ctx, int32_t variant);
 
 /* Number of launch shapes (for lbm_set_variant) and a short description. */
@@ -216,7 +216,7 @@ const char *lbm_variant_name(const lbm_ctx_t *ctx, int32_t variant);
  * step into on-chip memory and the next from there; up to 64 for the D2Q9
  * on-chip window shapes (single lattices, every rule; as many as a window
  * holds at the lattice's size); 2, 3 or 4 for the D2Q9 register pipelines
- * (single lattices, every rule), which pass each row from step to step in
+ * (single lattices and batches, every rule), which pass each row from step to step in
  * registers; 32 for the D1Q3 shapes that keep the nodes in registers.  HBM
  * then sees one read and one write of every population per launch.
  * Results are bitwise equal to single steps, status records included;

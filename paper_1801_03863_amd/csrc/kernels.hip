@@ -1561,10 +1561,29 @@ constexpr ShapeB kShapesB9[] = {{256, 1, "batch 256 nodes/block"}, {128, 1, "bat
                                 {256, 1, "batch two steps per launch, 256x16 tiles, split rings, nt-load(unshifted planes) nt-store, XCD-banded", 2, 16},
                                 {64, 1, "batch two steps per launch, 64x16 tiles, split rings, nt-load(unshifted planes) nt-store, XCD-banded", 2, 16},
                                 {128, 1, "batch two steps per launch, 128x16 tiles, 3-row ring, nt-load(unshifted planes) nt-store", 2, 16},
-                                {128, 1, "batch two steps per launch, 128x16 tiles, split rings, nt-load(unshifted planes) nt-store", 2, 16}};
-// Single-step batch shapes (every collision rule); the rest of kShapesB9 are
-// two-step shapes of MinxEnt4.
+                                {128, 1, "batch two steps per launch, 128x16 tiles, split rings, nt-load(unshifted planes) nt-store", 2, 16},
+                                // register pipelines (every collision rule): blk = 64 - 2 (steps - 1) columns
+                                {62, 1, "batch register pipeline, 2 steps per launch, 62x8 tiles", 2, 8},
+                                {62, 1, "batch register pipeline, 2 steps per launch, 62x16 tiles", 2, 16},
+                                {62, 1, "batch register pipeline, 2 steps per launch, 62x32 tiles", 2, 32},
+                                {60, 1, "batch register pipeline, 3 steps per launch, 60x16 tiles", 3, 16},
+                                {60, 1, "batch register pipeline, 3 steps per launch, 60x32 tiles", 3, 32},
+                                {58, 1, "batch register pipeline, 4 steps per launch, 58x16 tiles", 4, 16},
+                                {58, 1, "batch register pipeline, 4 steps per launch, 58x32 tiles", 4, 32}};
+// Single-step batch shapes (every collision rule), then two-step shapes of
+// MinxEnt4, then register pipelines (every rule).
 constexpr int kNumB9One = 9;
+constexpr int kNumB9Pipes = 7;
+constexpr int kNumB9 = sizeof(kShapesB9) / sizeof(kShapesB9[0]);
+constexpr int kFirstB9Pipe = kNumB9 - kNumB9Pipes;
+
+// Entry of kShapesB9 of shape v of a collision rule, or -1.
+int shape_of_b9(int coll, int v)
+{
+    if (v < 0) return -1;
+    if (coll != CO_MINXENT4 && v >= kNumB9One) v += kFirstB9Pipe - kNumB9One;
+    return v < kNumB9 ? v : -1;
+}
 constexpr ShapeB kShapesB3[] = {{256, 1, "batch 256x1 nodes/block"}, {128, 1, "batch 128x1 nodes/block"},
                                 {256, 4, "batch 256x4 nodes/block"}, {256, 8, "batch 256x8 nodes/block"},
                                 {256, 4, "batch 256x4 nodes/block nt-load nt-store"},
@@ -1702,17 +1721,17 @@ const char *d2q9_variant_name(int coll, int v)
 }
 int d1q3_variant_count() { return kNumShapes3; }
 const char *d1q3_variant_name(int v) { return (v >= 0 && v < kNumShapes3) ? kShapes3[v].name : "?"; }
-constexpr int kNumB9 = sizeof(kShapesB9) / sizeof(kShapesB9[0]);
 constexpr int kNumB3 = sizeof(kShapesB3) / sizeof(kShapesB3[0]);
 int batch_variant_count(int lattice, int coll)
 {
     if (lattice == 3) return kNumB3;
-    return coll == CO_MINXENT4 ? kNumB9 : kNumB9One;
+    return coll == CO_MINXENT4 ? kNumB9 : kNumB9One + kNumB9Pipes;
 }
-int batch_variant_steps(int lattice, int v)
+int batch_variant_steps(int lattice, int coll, int v)
 {
     if (lattice == 3) return (v >= 0 && v < kNumB3) ? kShapesB3[v].steps : 1;
-    return (v >= 0 && v < kNumB9) ? kShapesB9[v].steps : 1;
+    const int k = shape_of_b9(coll, v);
+    return k >= 0 ? kShapesB9[k].steps : 1;
 }
 int d1q3_variant_steps(int v) { return (v >= 0 && v < kNumShapes3) ? kShapes3[v].steps : 1; }
 
@@ -1725,16 +1744,34 @@ int d1q3_default_variant(int batch, int64_t nodes)
     const int i = nodes < 400000 ? 0 : (nodes < 3000000 ? 1 : 2);  // 2, 4 or 8 nodes per lane
     return (batch ? kFirstRegsB3 : kFirstRegs3) + i;
 }
-int batch_tile_nodes(int lattice, int v)
+int batch_tile_nodes(int lattice, int coll, int v)
 {
     if (lattice == 3) return (v >= 0 && v < kNumB3) ? kShapesB3[v].blk * kShapesB3[v].npt : 0;
-    if (v < 0 || v >= kNumB9) return 0;
-    if (kShapesB9[v].steps == 2) return -(kShapesB9[v].blk * 4096 + kShapesB9[v].rows);
-    return kShapesB9[v].blk * kShapesB9[v].npt;
+    const int k = shape_of_b9(coll, v);
+    if (k < 0) return 0;
+    if (kShapesB9[k].rows) return -(kShapesB9[k].blk * 4096 + kShapesB9[k].rows);
+    return kShapesB9[k].blk * kShapesB9[k].npt;
 }
+
+// A wave of a register pipeline takes some 50 collisions one after another per
+// launch; one step per launch of a batch too small for two waves per SIMD does
+// not wait for that (22 thousand nodes of 12 lattices: 5,700 MLUPS against 1,600;
+// a quarter million of 8 cavities: 38,000 against 22,000).  Beyond, three steps
+// lead in FP64 and FP32 and two in the other forms, which are bound by issue
+// (128 cavities, 5.2 million nodes, MLUPS, one step per launch / two-step rings /
+// pipeline of two steps / of three: FP64 35,700 / 49,500 / 45,700 / 56,100, FP32
+// 71,000 / 84,300 / 88,300 / 94,700, FP32 storage / FP64 compute 63,500 / 58,700 /
+// 72,000 / 66,300, SRT FP32 69,000 / - / 93,600 / 124,000).
+int batch_default_variant(int st, int coll, int64_t waves)
+{
+    if (waves < 2048) return 0;
+    const bool three = st == ST_F64 || st == ST_F32;
+    return batch_variant_count(9, coll) - kNumB9Pipes + (three ? 3 : 1);
+}
+
 hipError_t prepare_batch_variant(int st, int coll, int v)
 {
-    if (coll != CO_MINXENT4 || batch_variant_steps(9, v) != 2) return hipSuccess;
+    if (coll != CO_MINXENT4 || v < kNumB9One || v >= kFirstB9Pipe) return hipSuccess;
     const StepArgs none{};
     switch (st) {
     case ST_F64: return dispatch9bt2<ST_F64, CO_MINXENT4>(v, true, nullptr, nullptr, none, nullptr);
@@ -1744,10 +1781,11 @@ hipError_t prepare_batch_variant(int st, int coll, int v)
     default: return hipErrorInvalidValue;
     }
 }
-const char *batch_variant_name(int lattice, int v)
+const char *batch_variant_name(int lattice, int coll, int v)
 {
     if (lattice == 3) return (v >= 0 && v < kNumB3) ? kShapesB3[v].name : "?";
-    return (v >= 0 && v < kNumB9) ? kShapesB9[v].name : "?";
+    const int k = shape_of_b9(coll, v);
+    return k >= 0 ? kShapesB9[k].name : "?";
 }
 
 bool d2q9_variant_pipe(int coll, int v) { return shape_of(coll, v) >= kFirstPipe; }
@@ -1789,22 +1827,25 @@ int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
 }
 
 namespace {
-hipError_t launch_d2q9_pipe(int st, int coll, const void *src, void *dst, const StepArgs &a_in, hipStream_t s)
+hipError_t launch_d2q9_pipe(int st, int coll, int k, int batch, const void *src, void *dst, const StepArgs &a_in,
+                            hipStream_t s)
 {
     StepArgs a = a_in;
     if (a.tile_rows < 1) return hipErrorInvalidValue;
-    const int w = 64 - 2 * (a.max_steps - 1);
-    a.tiles_x = (a.one.nx + w - 1) / w;
-    const int64_t tiles = (int64_t)a.tiles_x * ((a.one.ny + a.tile_rows - 1) / a.tile_rows);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    a.ntiles = (int32_t)tiles;
+    if (!batch) {
+        const int w = 64 - 2 * (k - 1);
+        a.tiles_x = (a.one.nx + w - 1) / w;
+        const int64_t tiles = (int64_t)a.tiles_x * ((a.one.ny + a.tile_rows - 1) / a.tile_rows);
+        if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+        a.ntiles = (int32_t)tiles;
+    }
     a.xcd_swizzle = 1;  // adjacent tiles share lines: let them share an L2
     switch (coll) {
-    case CO_MINXENT4: return launch_d2q9_pipe_0(st, src, dst, a, s);
-    case CO_MINXENT2: return launch_d2q9_pipe_1(st, src, dst, a, s);
-    case CO_SRT: return launch_d2q9_pipe_2(st, src, dst, a, s);
-    case CO_TRT: return launch_d2q9_pipe_3(st, src, dst, a, s);
-    case CO_MRT: return launch_d2q9_pipe_4(st, src, dst, a, s);
+    case CO_MINXENT4: return launch_d2q9_pipe_0(st, k, batch, src, dst, a, s);
+    case CO_MINXENT2: return launch_d2q9_pipe_1(st, k, batch, src, dst, a, s);
+    case CO_SRT: return launch_d2q9_pipe_2(st, k, batch, src, dst, a, s);
+    case CO_TRT: return launch_d2q9_pipe_3(st, k, batch, src, dst, a, s);
+    case CO_MRT: return launch_d2q9_pipe_4(st, k, batch, src, dst, a, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1814,7 +1855,7 @@ hipError_t launch_d2q9_step(int st, int coll, int v, const void *src, void *dst,
 {
     if (v < 0 || v >= d2q9_variant_count(coll)) return hipErrorInvalidValue;
     const int k = shape_of(coll, v);
-    if (k >= kFirstPipe && a.max_steps > 1) return launch_d2q9_pipe(st, coll, src, dst, a, s);
+    if (k >= kFirstPipe && a.max_steps > 1) return launch_d2q9_pipe(st, coll, a.max_steps, 0, src, dst, a, s);
     if (k >= kFirstPipe) v = 0;  // one step
     else if (k >= kFirstWindow) return launch_d2q9_window(st, coll, src, dst, a, s);
     switch (st) {
@@ -1829,7 +1870,13 @@ hipError_t launch_d2q9_step(int st, int coll, int v, const void *src, void *dst,
 hipError_t launch_d2q9_batch_step(int st, int coll, int v, const void *src, void *dst, const StepArgs &a,
                                   hipStream_t s)
 {
-    if (v < 0 || v >= batch_variant_count(9, coll)) return hipErrorInvalidValue;
+    v = shape_of_b9(coll, v);
+    if (v < 0) return hipErrorInvalidValue;
+    if (v >= kFirstB9Pipe) {
+        StepArgs p = a;
+        p.tile_rows = kShapesB9[v].rows;
+        return launch_d2q9_pipe(st, coll, kShapesB9[v].steps, 1, src, dst, p, s);
+    }
     switch (st) {
     case ST_F64: return dispatch9bc<ST_F64>(coll, v, src, dst, a, s);
     case ST_F32N64: return dispatch9bc<ST_F32N64>(coll, v, src, dst, a, s);

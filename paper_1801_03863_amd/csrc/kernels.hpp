@@ -93,16 +93,22 @@ bool d2q9_window_plan(int storage, int coll, int nx, int ny, int bc, int k, Wind
 hipError_t launch_d2q9_window(int storage, int coll, const void *src, void *dst, const StepArgs &a, hipStream_t s);
 // Register-pipeline shapes (pipeline.hip): whether a shape is one; the tile
 // rows for launches of k steps of one lattice, with the estimated
-// microseconds per step; and one launcher per collision rule for
-// a.max_steps steps (2 to 4) with tiles of a.tile_rows rows.
+// microseconds per step; and one launcher per collision rule, for
+// windows of k steps (2 to 4; a batch may take fewer, a single lattice takes
+// k) with tiles of a.tile_rows rows.
 bool d2q9_variant_pipe(int coll, int variant);
 int d2q9_variant_rows(int coll, int variant);  // fixed tile rows of such a shape, or 0: d2q9_pipe_rows
 int d2q9_pipe_rows(int storage, int coll, int nx, int ny, int k, double *us_per_step);
-hipError_t launch_d2q9_pipe_0(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
-hipError_t launch_d2q9_pipe_1(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
-hipError_t launch_d2q9_pipe_2(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
-hipError_t launch_d2q9_pipe_3(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
-hipError_t launch_d2q9_pipe_4(int storage, const void *src, void *dst, const StepArgs &a, hipStream_t s);
+hipError_t launch_d2q9_pipe_0(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
+                              hipStream_t s);
+hipError_t launch_d2q9_pipe_1(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
+                              hipStream_t s);
+hipError_t launch_d2q9_pipe_2(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
+                              hipStream_t s);
+hipError_t launch_d2q9_pipe_3(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
+                              hipStream_t s);
+hipError_t launch_d2q9_pipe_4(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
+                              hipStream_t s);
 int d1q3_variant_count();
 const char *d1q3_variant_name(int variant);
 int d1q3_variant_steps(int variant);  // steps one launch takes at most (StepArgs::max_steps sets fewer)
@@ -120,13 +126,15 @@ hipError_t launch_d1q3_regs(int storage, int n, int batch, const void *src, void
 hipError_t launch_d2q9_lds(int storage, int coll, const void *src, void *dst, const StepArgs &a, int nsteps,
                            int block, size_t smem_bytes, hipStream_t s);
 // Batched shapes: count (MinxEnt4 D2Q9 batches also have two-step shapes),
-// steps per launch, nodes per tile of the tile table (negative for the 2D
-// tiles of a two-step shape: -(width * 4096 + rows)), name, and the
-// host-side set-up before a shape's first launch.
+// steps per launch, nodes per tile of the tile table (negative for 2D tiles:
+// -(width * 4096 + rows)), name, the shape a D2Q9 batch starts in (waves: 2D
+// tiles of 62 x 16 nodes it holds), and the host-side set-up before a shape's
+// first launch.
 int batch_variant_count(int lattice, int coll);
-int batch_variant_steps(int lattice, int variant);
-int batch_tile_nodes(int lattice, int variant);
-const char *batch_variant_name(int lattice, int variant);
+int batch_variant_steps(int lattice, int coll, int variant);
+int batch_tile_nodes(int lattice, int coll, int variant);
+const char *batch_variant_name(int lattice, int coll, int variant);
+int batch_default_variant(int storage, int coll, int64_t waves);
 hipError_t prepare_batch_variant(int st, int coll, int variant);
 
 // Nodes [g0, g1) of all instances counted one after another.

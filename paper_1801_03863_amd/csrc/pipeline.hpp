@@ -1,4 +1,4 @@
-// pipeline.hpp -- D2Q9, one lattice, K steps per launch with everything
+// pipeline.hpp -- D2Q9, one lattice or a batch, K steps per launch with everything
 // between the first pull and the last store in registers.
 //
 // A wave owns an output tile of 64 - 2 (K - 1) columns and H rows, and walks
@@ -27,7 +27,9 @@
 // each other at every row.  Measured on the 4096^2 cavity, us per step, best
 // shape before -> here: FP64 250 -> 221, FP32 storage / FP64 compute 187 -> 178,
 // FP32 129 -> 119, FP16 deviations 119.5 -> 115.5, MRT FP64 432 -> 157, SRT FP32
-// 213 -> 82; 2048^2 FP64 74 -> 61-65; 1000^2 MRT FP64 24.2 -> 15.0.
+// 213 -> 82; 2048^2 FP64 74 -> 61-65; 1000^2 MRT FP64 24.2 -> 15.0.  Batches, MLUPS:
+// 512 cavities FP32 103,500 -> 118,000, FP64 57,000 -> 63,000; 128 cavities SRT FP32
+// 69,000 -> 147,000, MRT FP64 35,700 -> 61,000.
 #pragma once
 
 #include <type_traits>
@@ -45,29 +47,52 @@ struct StageRows {
     T a4, a7, a8;  // read again only at a top wall
 };
 
-template <int ST, int CO, int K>
-__global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__restrict__ src,
-                                                  typename Form<ST>::T *__restrict__ dst, StepArgs a)
+template <int ST, int CO, int K, bool BATCH>
+__global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__restrict__ src_all,
+                                                 typename Form<ST>::T *__restrict__ dst_all, StepArgs a)
 {
     using C = typename Form<ST>::C;
     using T = typename Form<ST>::T;
     constexpr int W = 64 - 2 * (K - 1);  // columns of a tile
-    const Inst &in = a.one;
-    const int nx = in.nx, ny = in.ny, pitch = in.pitch;
-    const int64_t P = in.plane;
+    const int b = a.xcd_swizzle ? xcd_remap((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+    const int entry = b * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (entry >= a.ntiles) return;  // wave-uniform
+    // A batch's tile table gives the instance and the tile within it.
+    const int ii = BATCH ? a.tile_inst[entry] : 0;
+    const int tile = BATCH ? a.tile_first[entry] : entry;
+    const Inst &lat = BATCH ? a.inst[ii] : a.one;
+    Inst in;  // what the collision reads, held in registers
+    in.omega = lat.omega;
+    in.omega2 = lat.omega2;
+    in.rho0 = lat.rho0;
+    const int nx = lat.nx, ny = lat.ny, pitch = lat.pitch;
+    const int64_t P = lat.plane;
+    const T *src = src_all + (BATCH ? lat.offset : 0);
+    T *dst = dst_all + (BATCH ? lat.offset : 0);
     const int bc = a.bc;
     const bool xw = bc == BC_PERIODIC;
     const bool yw = bc == BC_PERIODIC || bc == BC_TUBE;
     const bool cavity = bc == BC_CAVITY;
-    const int b = a.xcd_swizzle ? xcd_remap((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-    const int tile = b * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (tile >= a.ntiles) return;  // wave-uniform
-    const int ty = tile / a.tiles_x, tx = tile - ty * a.tiles_x;
+    const int tiles_x = BATCH ? (nx + W - 1) / W : a.tiles_x;
+    const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
     const int H = a.tile_rows;
     const int lane = (int)(threadIdx.x & 63);
     const int x = tx * W - (K - 1) + lane, y0 = ty * H;
     const int yn = min(ny, y0 + H);  // own rows [y0, yn)
     const bool own_x = lane >= K - 1 && lane < 64 - (K - 1) && x < nx;
+    // Steps this wave takes (wave-uniform): K, or in a batch fewer for a launch
+    // of fewer steps or an instance that reaches its step limit, none for one
+    // that has (it carries its nodes over).
+    int kdo = K;
+    if constexpr (BATCH) {
+        const int64_t s0 = a.step + (a.step_base ? *a.step_base : 0);
+        kdo = (int)max((int64_t)0, min((int64_t)min(K, a.max_steps), lat.stop - s0));
+        if (kdo <= 0) {
+            if (own_x)
+                for (int y = y0; y < yn; ++y) carry_node(src, dst, P, 9, y * pitch + x);
+            return;
+        }
+    }
     int xs = x;  // lattice column of this lane
     if (xw) {
         if (xs < 0) xs += nx;
@@ -130,8 +155,11 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
         };
         auto lid = [&](T (&sv)[9]) {
             asm volatile("");  // a block of its own
+            const double *v = lat.lid;
+            // a table's values are read here, not kept in registers for every row
+            if constexpr (BATCH) asm volatile("" : "+s"(v));
 #pragma unroll
-            for (int q = 0; q < 9; ++q) sv[q] = to_storage<ST>(C(in.lid[q]), ref[q], a.fp16_scale);
+            for (int q = 0; q < 9; ++q) sv[q] = to_storage<ST>(C(v[q]), ref[q], a.fp16_scale);
         };
 
         T raw[9];
@@ -149,6 +177,7 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
                     node(f, 0, r, sv);
                 }
                 if (r + 1 <= last_row(1)) pull_row(r + 1, raw);  // completes during the other stages
+                if (BATCH && kdo == 1 && own_x && r >= y0 && r < yn) push9_xy_st<ST>(dst, P, x, r, pitch, sv);
             }
 #pragma unroll
             for (int s = 1; s < K; ++s) {
@@ -156,6 +185,7 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
                 // (unless y is the top row).
                 StageRows<T> &d = st[s - 1];
                 const int y = r - s;
+                if (BATCH && s >= kdo) break;
                 const bool run = y >= first_row(s + 1) && y <= last_row(s + 1);
                 T n4 = sv[4], n7 = lane_shift<false>(sv[7]), n8 = lane_shift<true>(sv[8]);
                 T t1 = lane_shift<true>(sv[1]), t3 = lane_shift<false>(sv[3]);
@@ -194,7 +224,9 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
                         f[8] = load<ST>(&n8, ref[8], a.fp16_iscale);
                         node(f, s, y, sv);
                     }
-                    if (s == K - 1) {
+                    if (BATCH) {
+                        if (s == kdo - 1 && own_x && y >= y0 && y < yn) push9_xy_st<ST>(dst, P, x, y, pitch, sv);
+                    } else if (s == K - 1) {
                         if (own_x) push9_xy_st<ST>(dst, P, x, y, pitch, sv);
                     }
                 }
@@ -218,7 +250,7 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
     if (!edge && y0 - K >= 0 && yn - 1 + K <= ny - 1) walk(std::true_type{});
     else walk(std::false_type{});
 #pragma unroll
-    for (int s = 0; s < K; ++s) report(a.status, bad[s], s == 0 ? guarded : 0, a.step + s, a.step_base);
+    for (int s = 0; s < K; ++s) report(a.status + ii, bad[s], s == 0 ? guarded : 0, a.step + s, a.step_base);
 }
 
 }  // namespace lbm

@@ -255,8 +255,8 @@ int build_tiles(lbm_ctx *c, int tile_nodes)
 {
     std::vector<int32_t> ti, tf;
     if (tile_nodes < 0) {
-        // Two-step shapes: tiles of bx x rows nodes, row-major within each
-        // instance, recorded as the tile's index ty * tiles_x + tx.
+        // 2D tiles of bx x rows nodes, row-major within each instance, recorded
+        // as the tile's index ty * tiles_x + tx.
         const int bx = -tile_nodes / 4096, rows = -tile_nodes % 4096;
         for (int i = 0; i < c->n; ++i) {
             const int64_t nt = (int64_t)((c->inst[i].nx + bx - 1) / bx) * ((c->inst[i].ny + rows - 1) / rows);
@@ -384,8 +384,8 @@ int pipe_rows(const lbm_params_t &p, int v)
 int launch_steps(const lbm_ctx *c, int v)
 {
     if (v == c->variant) return c->spl;
-    if (c->b != 9) return c->batch ? lbm::batch_variant_steps(3, v) : lbm::d1q3_variant_steps(v);
-    if (c->batch) return v == c->lds_variant ? 1 : lbm::batch_variant_steps(9, v);
+    if (c->b != 9) return c->batch ? lbm::batch_variant_steps(3, c->p.collision, v) : lbm::d1q3_variant_steps(v);
+    if (c->batch) return v == c->lds_variant ? 1 : lbm::batch_variant_steps(9, c->p.collision, v);
     if (lbm::d2q9_variant_window(c->p.collision, v)) {
         lbm::WindowTile tile;
         return window_plan(c->p, v, &tile);
@@ -851,13 +851,20 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
         CK(hipMalloc(&c->d_inst, table + numbers));
         c->d_prefix = (int64_t *)((char *)c->d_inst + table);
         CK(hipMemcpy(c->d_inst, both.data(), table + numbers, hipMemcpyHostToDevice));
-        rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->b == 3 ? lbm::d1q3_default_variant(1, c->nodes) : 0));
+        int v = lbm::d1q3_default_variant(1, c->nodes);
+        if (c->b == 9) {
+            int64_t waves = 0;
+            for (const Inst &in : c->inst) waves += (int64_t)((in.nx + 61) / 62) * ((in.ny + 15) / 16);
+            v = lbm::batch_default_variant(c->storage, c->p.collision, waves);
+        }
+        use_variant(c, v);
+        rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
         if (rc) {
             destroy(c);
             return rc;
         }
     }
-    if (c->b == 3) use_variant(c, lbm::d1q3_default_variant(batch, c->nodes));
+    if (!batch && c->b == 3) use_variant(c, lbm::d1q3_default_variant(0, c->nodes));
     else if (!batch) use_variant(c, lbm::d2q9_default_variant(c->storage, c->p.collision, c->p.nx, c->p.ny, c->p.bc));
     CK(lbm::launch_clear_status(c->d_status, 2 * n, c->stream));  // the step base is set before a graph reads it
 #undef CK
@@ -1011,8 +1018,8 @@ int lbm_set_variant(lbm_ctx_t *c, int32_t v)
     if (c->batch && c->b == 9 && v != c->lds_variant)
         HIPCHK(lbm::prepare_batch_variant(c->storage, c->p.collision, v));
     use_variant(c, v);
-    if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, v) != c->tile_nodes)
-        return build_tiles(c, lbm::batch_tile_nodes(c->b, v));
+    if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, c->p.collision, v) != c->tile_nodes)
+        return build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
     return LBM_OK;
 }
 
@@ -1060,7 +1067,7 @@ const char *lbm_variant_name(const lbm_ctx_t *c, int32_t v)
 {
     if (!c) return "?";
     if (c->batch && v == c->lds_variant && v >= 0) return "batch persistent, lattices resident in LDS";
-    if (c->batch) return lbm::batch_variant_name(c->b, v);
+    if (c->batch) return lbm::batch_variant_name(c->b, c->p.collision, v);
     return c->b == 9 ? lbm::d2q9_variant_name(c->p.collision, v) : lbm::d1q3_variant_name(v);
 }
 

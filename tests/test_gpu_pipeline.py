@@ -87,3 +87,62 @@ def test_contexts_and_noalloc_start_in_a_pipeline_beyond_the_windows(coll, prec,
     assert b.lbm_run_noalloc(p, *t, 7, *out) == ref["status"]
     for name, a in zip(("rho", "ux", "uy"), out):
         assert np.array_equal(ref[name].reshape(-1), a.cpu().numpy()), name
+
+
+@pytest.mark.parametrize("bc", ["cavity", "periodic", "box"])
+@pytest.mark.parametrize("coll,prec", [("minxent4", "fp64"), ("minxent4", "fp32"), ("minxent4", "fp16dev"),
+                                       ("minxent2", "fp32_newton64"), ("srt", "fp64"), ("mrt", "fp16dev")])
+def test_batch_pipelines_equal_single_steps(bc, coll, prec):
+    # widths and heights around the tiles; step limits before, inside and after
+    # launches of 2, 3 and 4 steps; plain launches and graphs
+    b = B()
+    sizes = [(3, 3), (58, 8), (60, 33), (62, 16), (63, 17), (125, 9), (7, 150), (250, 70), (64, 64)]
+    limits = [-1, 0, 1, 2, 3, 5, 11, -1, 8]
+    params = [b.make_params("d2q9", coll, bc, prec, nx, ny, 0.58 + 0.01 * k, 0.0, 0.05, 1.0)
+              for k, (nx, ny) in enumerate(sizes)]
+    fields = [smooth_fields(nx, ny, seed=300 + k) for k, (nx, ny) in enumerate(sizes)]
+    rho, ux, uy = (np.concatenate([f[i].reshape(-1) for f in fields]) for i in range(3))
+
+    def run(v, steps, graph, limited):
+        ctx = b.lbm_init_batch(params, rho, ux, uy)
+        try:
+            if v is None:
+                return [v for v in range(b.lbm_variant_count(ctx)) if "register pipeline" in b.lbm_variant_name(ctx, v)]
+            b.lbm_set_variant(ctx, v)
+            if limited:
+                b.lbm_set_batch_steps(ctx, limits)
+            if graph:
+                b.lbm_set_graph_chunk(ctx, graph)
+            for n in steps:
+                b.lbm_step(ctx, n)
+            return b.lbm_get_populations(ctx, 9), b.lbm_status_batch(ctx, len(sizes))
+        finally:
+            b.lbm_free(ctx)
+
+    shapes = run(None, (), 0, False)
+    assert len(shapes) == 7
+    for steps, graph, limited in (((12,), 0, False), ((1, 10), 0, True), ((14,), 5, True)):
+        ref = run(0, steps, 0, limited)
+        for v in shapes:
+            got = run(v, steps, graph, limited)
+            assert np.array_equal(ref[0], got[0]), (v, steps, graph, limited)
+            assert ref[1] == got[1], (v, steps, graph, limited)
+
+
+def test_large_batches_start_in_a_pipeline():
+    b = B()
+    sizes = [(300, 300)] * 30 + [(40, 500)] * 4
+    params = [b.make_params("d2q9", "minxent4", "cavity", "fp32", nx, ny, 0.6, 0.0, 0.05, 1.0) for nx, ny in sizes]
+    fields = [smooth_fields(nx, ny, seed=k) for k, (nx, ny) in enumerate(sizes)]
+    rho, ux, uy = (np.concatenate([f[i].reshape(-1) for f in fields]) for i in range(3))
+    got = []
+    for v in (0, None):
+        ctx = b.lbm_init_batch(params, rho, ux, uy)
+        try:
+            if v is not None:
+                b.lbm_set_variant(ctx, v)
+            b.lbm_step(ctx, 7)
+            got.append((b.lbm_get_populations(ctx, 9), b.lbm_status_batch(ctx, len(sizes))))
+        finally:
+            b.lbm_free(ctx)
+    assert np.array_equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
