@@ -1668,20 +1668,24 @@ bool d2q9_variant_window(int coll, int v)
     return k >= kFirstWindow && k < kFirstPipe;
 }
 
-// One-step launches cost about 4.3 us each up to some 60k nodes and then
-// 3 us + 23 ps per node (FP64, 257^2 to 1000^2: 6.1, 8.4, 10.3, 11.2, 18.5 and
-// 24.9 us at 257, 400, 512, 600, 800 and 1000; FP32 about three quarters of
-// that from 600^2 on), and the bytes of a step beyond the caches (1400^2 55 us,
-// 2048^2 110 us).  The window shapes take 1.6 us per step at 32^2, 2.0 at
-// 128^2, 3.6 at 257^2 and 8.1 at 512^2, so they lead up to about 550^2; the
+// The longer of two times that overlap, a little more where they are close.
+static double soft_max(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
+
+// One-step launches cost 4.6 us each and 18 ps per node (FP64 MinxEnt; 5-17 in
+// the others), and the bytes of a step at 6.2 TB/s beyond the caches (FP64,
+// us per step: 6.1, 8.4, 11.2, 24.9, 55 and 110 at 257^2, 400^2, 600^2, 1000^2,
+// 1400^2 and 2048^2).  The window shapes take 1.6 us per step at 32^2, 2.0 at
+// 128^2, 3.6 at 257^2 and 7.5 at 480^2, so they lead up to about 550^2; the
 // register pipelines lead from there on (FP64 MinxEnt4 / MRT, us per step:
 // 1000^2 21.6 / 16.5, 2048^2 61 / 50, 4096^2 221 / 157, against 24.9 / 24.1,
 // 110 / 109 and 430 / 432 for one step per launch).
 int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
 {
     const int windows = d2q9_variant_count(coll) - kNumPipes - kNumWindows;
+    const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
     const double nodes = (double)nx * ny, elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
-    double best = std::max({4.3, 3.0 + (st == ST_F64 ? 2.3e-5 : 1.7e-5) * nodes, nodes * 18 * elem / 5.5e6});
+    const double node_ps[2][4] = {{16.7, 8.8, 8.2, 5.4}, {18.4, 8.5, 9.7, 6.6}};
+    double best = soft_max(4.6 + node_ps[newton][st] * 1e-6 * nodes, nodes * 18 * elem / 6.2e6);
     int v = 0;
     for (int k = 0; k < kNumWindows; ++k) {
         WindowTile tile;
@@ -1691,7 +1695,9 @@ int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
             v = windows + k;
         }
     }
-    for (int k = 0; k < 3; ++k) {  // the shapes whose rows go by the lattice
+    // The shapes whose rows go by the lattice; more steps only if they gain more
+    // than the estimates are off by (600^2 FP64: 9.5 us with two, 10.1 with three).
+    for (int k = 0; k < 3; ++k) {
         double us = 0;
         d2q9_pipe_rows(st, coll, nx, ny, kShapes[kFirstPipe + k].steps, &us);
         if (us < 0.95 * best) {
@@ -1800,7 +1806,12 @@ int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
     const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
     // Waves per SIMD the kernel's registers allow.
     const int occ = st == ST_F64 ? (newton ? 6 - k : 7 - k) : (st == ST_F32N64 && newton ? 4 : 6);
-    const double latency = newton ? 1950 : 1000, issue = newton ? 1550 : 700;  // cycles of one collision
+    // Microseconds of one collision of a wave: its latency, and its issue.  Fitted
+    // with the fixed time and the rate below to 7,200 launches (60,000 nodes to
+    // 3500^2, 4 to 32 rows, every rule and form; off by 5-9% rms).
+    const double latency_of[2][4] = {{0.65, 0.54, 0.55, 0.56}, {1.08, 0.98, 0.85, 0.89}};
+    const double issue_of[2][4] = {{0.40, 0.32, 0.22, 0.29}, {0.68, 0.63, 0.40, 0.45}};
+    const double latency = latency_of[newton][st], issue = issue_of[newton][st];
     const double elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
     const int w = 64 - 2 * (k - 1);
     const int64_t strips = (nx + w - 1) / w;
@@ -1809,14 +1820,13 @@ int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
     for (int h = 1; h <= 48; ++h) {
         if (h > ny) break;
         const int64_t blocks = (strips * ((ny + h - 1) / h) + 3) / 4;
-        // Blocks per compute unit: whole while few are resident at once, on
-        // average (and part of a block of tail) when they come and go.
+        // Blocks per compute unit: whole while all are resident at once; on
+        // average, and in FP64 half a block of tail, when they come and go.
         const double mean = (double)blocks / kWindowCus, whole = std::ceil(mean);
-        const double r = whole <= 3 && whole <= occ ? whole : mean + 0.6;
-        const double collisions = k * h + k * (k - 1);  // of one wave
-        const double compute = collisions * std::max(latency, r * issue);
-        const double bytes = (double)nx * ny * 9 * elem * (2.1 + 0.6 * k / h);
-        const double us = 4.0 + std::max(compute / 2200, bytes / 5.5e6);
+        const double r = whole <= occ ? whole : mean + (st == ST_F64 ? 0.55 : 0.0);
+        const double compute = (k * h + k * (k - 1)) * soft_max(latency, r * issue);  // collisions of one wave
+        const double memory = (double)nx * ny * 9 * elem * (2.1 + 0.6 * k / h) / 5.2e6;
+        const double us = 4.8 + soft_max(compute, memory);
         if (best == 0 || us < best) {
             best = us;
             rows = h;

@@ -262,15 +262,18 @@ int d2q9_window_cap(int st) { return (int)std::min<size_t>(1024, 65536 / (9 * el
 
 bool d2q9_window_plan(int st, int coll, int nx, int ny, int bc, int k, WindowTile *out, double *us_per_step)
 {
-    // Time of a launch in us: a fixed part (launch, arguments, mapping), the
-    // lattice's bytes at the rate small launches reach, and per step the
-    // longer of one collision's latency and the issue time of the W waves
-    // that share a SIMD.  Fitted to launches of 1 to 8 steps of 32^2, 128^2 and
-    // 257^2 lattices in FP64 (MinxEnt4 / SRT): 1.2 / 0.55 us per step at one
-    // wave, 2.2 / 1.4 at two; 2.6 us of fixed time; 3.6 us more for 257^2.
+    // Time of a launch in us: a fixed part (launch, mapping, first loads), the
+    // lattice's bytes at the rate of launches whose state the caches hold, and
+    // per step the exchange through LDS and the issue of the waves that share
+    // a SIMD; the blocks of a compute unit that its LDS (160 KiB) or registers do
+    // not hold at once come one after another.  Fitted to 4,500 launches of 4 to
+    // 64 steps (12^2 to 1600^2, every rule and form): off by 7-15% rms, by 15-28%
+    // before the blocks in turn were counted.
     const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
-    const double latency = newton ? 1.25 : 0.65, base = newton ? 0.45 : 0.3, issue = newton ? 0.75 : 0.45;
-    const double fixed = 2.5 + (double)nx * ny * 18 * elem_of(st) / 2.6e6;
+    const double issue_of[2][4] = {{0.66, 0.64, 0.39, 0.41}, {0.95, 0.89, 0.64, 0.66}};
+    const double issue = issue_of[newton][st], exchange = 0.3;
+    const double fixed = 5.3 + (double)nx * ny * 18 * elem_of(st) / 18e6;
+    const int simd_waves = newton && (st == ST_F64 || st == ST_F32N64) ? 4 : (newton || st == ST_F64 ? 7 : 8);
     const int cap = d2q9_window_cap(st);
     const bool xw = bc == BC_PERIODIC, yw = bc == BC_PERIODIC || bc == BC_TUBE;
     double best = 0;
@@ -278,16 +281,21 @@ bool d2q9_window_plan(int st, int coll, int nx, int ny, int bc, int k, WindowTil
         if (tw0 > nx) break;
         const int gx = (nx + tw0 - 1) / tw0, tw = (nx + gx - 1) / gx;
         // Rows: the fewest that give each compute unit r blocks.
-        for (int r = 1; r <= 4; ++r) {
+        for (int r = 1; r <= 6; ++r) {
             const int gy0 = std::max(1, std::min(ny, kWindowCus * r / gx));
             const int th = (ny + gy0 - 1) / gy0, gy = (ny + th - 1) / th;
             if (win_extent(tw, nx, gx == 1, xw, k - 1) * (int64_t)win_extent(th, ny, gy == 1, yw, k - 1) > cap) continue;
-            const int per_cu = (int)(((int64_t)gx * gy + kWindowCus - 1) / kWindowCus);
+            const int m0 = win_extent(tw, nx, gx == 1, xw, k - 1) * win_extent(th, ny, gy == 1, yw, k - 1);
+            const int resident = std::max(1, std::min((int)(163840 / (9 * elem_of(st) * m0)),
+                                                      4 * simd_waves / ((m0 + 63) / 64)));
             double c = fixed;
-            for (int d = k - 1; d >= 0; --d) {
-                const int m = win_extent(tw, nx, gx == 1, xw, d) * win_extent(th, ny, gy == 1, yw, d);
-                const int waves = per_cu * ((m + 63) / 64);
-                c += std::max(latency, base + issue * ((waves + 3) / 4));
+            for (int left = (int)(((int64_t)gx * gy + kWindowCus - 1) / kWindowCus); left > 0; left -= resident) {
+                const int blocks = std::min(left, resident);
+                for (int d = k - 1; d >= 0; --d) {
+                    const int m = win_extent(tw, nx, gx == 1, xw, d) * win_extent(th, ny, gy == 1, yw, d);
+                    c += exchange + issue * std::max(1.0, blocks * ((m + 63) / 64) / 4.0);
+                }
+                if (best != 0 && c >= best) break;
             }
             if (best == 0 || c < best) {
                 best = c;
