@@ -1107,25 +1107,43 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
     const int nv = variant_count(c);
     // Enough launches per shape to time at least ~2e8 node updates.
     const int reps = (int)std::max<int64_t>(3, std::min<int64_t>(50, 200000000 / std::max<int64_t>(1, c->nodes)));
-    // Time `n` launches of shape v (the source buffer is the current state
-    // and is never written: the persistent shape runs an odd number of
-    // steps, ending in the other buffer); best of `trials`, in ms per `reps`
-    // steps (a two-step shape takes two per launch).
-    auto time_shape = [&](int v, int n, int trials, float &out) -> int {
-        int rc = lbm_set_variant(c, v);
-        if (rc) return rc;
+    // A state that the caches hold only in part is timed as a run moves it, from
+    // one buffer to the other and back, with a copy of the state set aside:
+    // read over and over from one buffer it would come from the caches (FP16
+    // deviations, 3001 x 2203, 119 MB a buffer: the shape chosen that way takes 55.1
+    // us per step, the one chosen this way 50.1).
+    // Smaller states are timed from the current buffer alone, which is never
+    // written (the persistent shape runs an odd number of steps, ending in the
+    // other one), and so are states whose copy finds no memory.
+    const size_t state_bytes = buffer_bytes(c->elems, c->elem);
+    struct Aside {
+        char *p = nullptr;
+        ~Aside()
+        {
+            if (p) (void)hipFree(p);
+        }
+    } aside;
+    if (state_bytes >= ((size_t)32 << 20) && hipMalloc((void **)&aside.p, state_bytes) != hipSuccess) {
+        aside.p = nullptr;
+        (void)hipGetLastError();
+    }
+    // Time `n` launches of shape v; best of `trials`, in ms per `reps` steps (a
+    // two-step shape takes two per launch).
+    auto time_launches = [&](int v, int n, int trials, float &out) -> int {
         const bool pers = c->batch && v == c->lds_variant;
         const int pn = n | 1;
         const int spl = launch_steps(c, v);
         float best_t = 1e30f;
         for (int trial = 0; trial < trials; ++trial) {
+            int cur = c->cur;
             HIPCHK(hipEventRecord(e0, c->stream));
             if (pers) {
                 HIPCHK(launch_lds(c, c->d_status_scratch, 0, pn, 1));
             } else {
                 for (int r = 0; r < n; ++r) {
                     lbm::StepArgs a = step_args(c, c->d_status_scratch, 0, nullptr);
-                    HIPCHK(launch_steps_from(c, v, spl, c->cur, a, c->stream));
+                    HIPCHK(launch_steps_from(c, v, spl, cur, a, c->stream));
+                    if (aside.p) cur ^= 1;
                 }
             }
             HIPCHK(hipEventRecord(e1, c->stream));
@@ -1137,6 +1155,17 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
         }
         out = best_t;
         return LBM_OK;
+    };
+    auto time_shape = [&](int v, int n, int trials, float &out) -> int {
+        int rc = lbm_set_variant(c, v);
+        if (rc) return rc;
+        if (aside.p) HIPCHK(lbm::launch_copy(aside.p, c->buf[c->cur], state_bytes, c->stream));
+        rc = time_launches(v, n, trials, out);
+        if (aside.p) {
+            HIPCHK(lbm::launch_copy(c->buf[c->cur], aside.p, state_bytes, c->stream));
+            HIPCHK(c->stream ? hipStreamSynchronize(c->stream) : hipDeviceSynchronize());
+        }
+        return rc;
     };
     // Stage 1: every shape, a short warm-up then the best of three trials.
     std::vector<std::pair<float, int>> t1;
