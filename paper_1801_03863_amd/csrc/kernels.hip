@@ -1879,11 +1879,17 @@ int d2q9_variant_rows(int coll, int v)
     return k >= kFirstPipe ? kShapes[k].by : 0;
 }
 
+// Waves per SIMD that the registers of a register pipeline allow.
+static int pipe_waves(int st, int coll, int k)
+{
+    const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
+    return st == ST_F64 ? (newton ? 6 - k : 7 - k) : (st == ST_F32N64 && newton ? 4 : 6);
+}
+
 int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
 {
     const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
-    // Waves per SIMD the kernel's registers allow.
-    const int occ = st == ST_F64 ? (newton ? 6 - k : 7 - k) : (st == ST_F32N64 && newton ? 4 : 6);
+    const int occ = pipe_waves(st, coll, k);
     // Microseconds of one collision of a wave: its latency, and its issue.  Fitted
     // with the fixed time and the rate below to 7,200 launches (60,000 nodes to
     // 3500^2, 4 to 32 rows, every rule and form; off by 5-9% rms).
@@ -1923,11 +1929,28 @@ hipError_t launch_d2q9_pipe(int st, int coll, int k, int batch, const void *src,
     if (!batch) {
         const int w = 64 - 2 * (k - 1);
         a.tiles_x = (a.one.nx + w - 1) / w;
-        const int64_t tiles = (int64_t)a.tiles_x * ((a.one.ny + a.tile_rows - 1) / a.tile_rows);
+        const int rows = (a.one.ny + a.tile_rows - 1) / a.tile_rows;  // of tiles
+        a.tall = rows;
+        a.low_rows = a.tile_rows;
+        const int64_t held = (int64_t)kWindowCus * 4 * pipe_waves(st, coll, k);
+        const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
+        // Where the waves come and go, a quarter of those held at once take half
+        // the rows and run last, so that the chip empties in half the time; the
+        // rows they take twice cost less than that (us per step, one height /
+        // two: headline form 4096^2 179.8 / 175.2, FP64 223.4 / 220.1, FP16 deviations
+        // 3001 x 2203 51.2 / 48.9; half of the waves held, or a quarter of the rows:
+        // 1-2% slower).  Not for the other rules, which the memory bounds
+        // (SRT FP64 4096^2 151.8 / 151.6 to 155.7).
+        if (newton && (int64_t)a.tiles_x * rows > held && a.tile_rows >= 8) {
+            a.tall = std::max(0, rows - (int)((held / 4 + a.tiles_x / 2) / a.tiles_x));
+            a.low_rows = a.tile_rows / 2;
+        }
+        const int below = a.tall * a.tile_rows;
+        const int64_t tiles =
+            (int64_t)a.tiles_x * (a.tall + (std::max(0, a.one.ny - below) + a.low_rows - 1) / a.low_rows);
         if (tiles > 0x7fffffff) return hipErrorInvalidValue;
         a.ntiles = (int32_t)tiles;
     }
-    a.xcd_swizzle = 1;  // adjacent tiles share lines: let them share an L2
     switch (coll) {
     case CO_MINXENT4: return launch_d2q9_pipe_0(st, k, batch, src, dst, a, s);
     case CO_MINXENT2: return launch_d2q9_pipe_1(st, k, batch, src, dst, a, s);

@@ -56,6 +56,8 @@ struct StepArgs {
     int32_t ntiles;
     int32_t tiles_x;        // single D2Q9: tiles along x
     int32_t tile_rows;      // register pipeline: rows of a tile
+    int32_t tall;           // single register pipeline: tile rows of tile_rows rows; the rest have low_rows
+    int32_t low_rows;
     int32_t xcd_swizzle;
     float fp16_scale;       // FP16DEV: 2^k
     float fp16_iscale;      // 2^-k

@@ -54,7 +54,15 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
     using C = typename Form<ST>::C;
     using T = typename Form<ST>::T;
     constexpr int W = 64 - 2 * (K - 1);  // columns of a tile
-    const int b = a.xcd_swizzle ? xcd_remap((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+    // Adjacent tiles share lines: each XCD takes a band of the tall tiles, then
+    // one of the low ones.
+    int b = (int)blockIdx.x;
+    if constexpr (BATCH) {
+        b = xcd_remap(b, (int)gridDim.x);
+    } else {
+        const int t = a.tall * a.tiles_x / 4, n = (int)gridDim.x;
+        b = b < t ? xcd_remap(b, t) : t + xcd_remap(b - t, n - t);
+    }
     const int entry = b * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (entry >= a.ntiles) return;  // wave-uniform
     // A batch's tile table gives the instance and the tile within it.
@@ -75,9 +83,10 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
     const bool cavity = bc == BC_CAVITY;
     const int tiles_x = BATCH ? (nx + W - 1) / W : a.tiles_x;
     const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    const int H = a.tile_rows;
+    const bool low = !BATCH && ty >= a.tall;
+    const int H = low ? a.low_rows : a.tile_rows;
     const int lane = (int)(threadIdx.x & 63);
-    const int x = tx * W - (K - 1) + lane, y0 = ty * H;
+    const int x = tx * W - (K - 1) + lane, y0 = low ? a.tall * a.tile_rows + (ty - a.tall) * H : ty * H;
     const int yn = min(ny, y0 + H);  // own rows [y0, yn)
     const bool own_x = lane >= K - 1 && lane < 64 - (K - 1) && x < nx;
     // Steps this wave takes (wave-uniform): K, or in a batch fewer for a launch

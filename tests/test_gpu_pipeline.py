@@ -146,3 +146,29 @@ def test_large_batches_start_in_a_pipeline():
         finally:
             b.lbm_free(ctx)
     assert np.array_equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
+
+
+@pytest.mark.parametrize("coll,prec,bc,nx,ny", [("minxent4", "fp16dev", "cavity", 2500, 1301),
+                                                ("minxent4", "fp16dev", "periodic", 2480, 2600),
+                                                ("minxent2", "fp64", "box", 2501, 1111),
+                                                ("minxent4", "fp32_newton64", "tube", 3000, 1603)])
+def test_tiles_of_two_heights_equal_single_steps(coll, prec, bc, nx, ny):
+    # more tiles than the chip holds at once: the last ones have half the rows
+    b = B()
+    rho, ux, uy = smooth_fields(nx, ny, seed=17)
+    p = b.make_params("d2q9", coll, bc, prec, nx, ny, 0.6, 0.0, 0.05 if bc == "cavity" else 0.0, 1.0)
+    ctx = b.lbm_init(p, rho, ux, uy)
+    try:
+        f0 = b.lbm_get_populations(ctx, 9)
+        names = [b.lbm_variant_name(ctx, v) for v in range(b.lbm_variant_count(ctx))]
+        ref = None
+        for v in [0] + [v for v, nm in enumerate(names) if "register pipeline" in nm]:
+            b.lbm_set_variant(ctx, v)
+            b.lbm_set_populations(ctx, f0)
+            b.lbm_reset_status(ctx)
+            b.lbm_step(ctx, 13)
+            got = (b.lbm_get_populations(ctx, 9), b.lbm_status(ctx)["flags"])
+            ref = ref or got
+            assert np.array_equal(ref[0], got[0]) and ref[1] == got[1], names[v]
+    finally:
+        b.lbm_free(ctx)
