@@ -37,6 +37,13 @@ struct Inst {
     int64_t stop;    // batched: the instance takes no step from this step index on
 };
 
+// Byte offset of node (x, y) in a plane whose rows are `pitch` elements apart:
+// the row's in 64 bits, since a plane may hold 4 GiB and more.
+__host__ __device__ inline int64_t plane_bytes(int x, int y, int pitch, int elem)
+{
+    return (int64_t)y * pitch * elem + (int64_t)x * elem;
+}
+
 // Tile of the on-chip window shapes: tw x th nodes, gx x gy tiles.
 struct WindowTile {
     int32_t tw, th, gx, gy;

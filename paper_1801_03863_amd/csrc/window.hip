@@ -207,11 +207,10 @@ __global__ __launch_bounds__(1024) void k_d2q9_win(WinArgs a)
         }
     }
     if (own) {
-        char *b = (char *)a.dst;
+        char *b = (char *)a.dst + plane_bytes(x, y, a.pitch, (int)sizeof(T));
         const int64_t PB = a.plane * (int64_t)sizeof(T);
-        const uint32_t o = (uint32_t)(y * a.pitch + x) * (uint32_t)sizeof(T);
 #pragma unroll
-        for (int q = 0; q < 9; ++q) *(T *)(b + q * PB + o) = sv[q];
+        for (int q = 0; q < 9; ++q) *(T *)(b + q * PB) = sv[q];
     }
     // Status: rare events.  The smallest (step, node) of the wave, and one
     // addition per lane that kept start points.

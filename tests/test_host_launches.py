@@ -1,0 +1,49 @@
+"""Which kernels a call enqueues, and what it does when the runtime refuses
+something, seen on the CPU through a runtime that only records (recorded.py).
+Nothing here runs on a device."""
+import os
+import subprocess
+
+import pytest
+
+import recorded
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    lib = recorded.build_recorder(tmp_path_factory.mktemp("recorder"))
+    return lambda body, **kw: recorded.run(lib, body, **kw)
+
+
+def test_recorder_sees_the_launches_of_a_run(run):
+    run("""
+    c = single("d2q9", "minxent4", "cavity", "fp64", 300, 7)
+    ks = kernels()
+    assert [k[0] for k in ks] == ["k_clear_status", "k_init"], ks
+    B.lbm_set_variant(c, 0)
+    B.lbm_step(c, 3)
+    assert kernels() == [("k_d2q9", 2, 7, 256)] * 3
+    B.lbm_moments(c)
+    assert kernels() == [("k_gather", 9, 1, 256)]
+    B.lbm_free(c)
+    assert rec.rec_blocks() == 0
+    """)
+
+
+def test_store_offsets_of_planes_beyond_4_gib(tmp_path):
+    # the offset the window kernel stores at, evaluated by the host compiler:
+    # corners of the largest lattices the library takes (rows of whole 128-byte
+    # lines, fewer than 2^31 elements), against Python's integers
+    cases = [(nx, ny, (nx * e + 127) // 128 * 128 // e, e)
+             for e, nx, ny in ((8, 24000, 24000), (8, 33, 11_300_000), (4, 32767, 32767), (2, 3, (1 << 25) - 1), (8, 9, 7))]
+    src = tmp_path / "offsets.cpp"
+    src.write_text('#include <cstdio>\n#include "kernels.hpp"\nint main() {\n' + "".join(
+        'std::printf("%%lld\\n", (long long)lbm::plane_bytes(%d, %d, %d, %d));\n' % (nx - 1, ny - 1, p, e)
+        for nx, ny, p, e in cases) + "}\n")
+    csrc = os.path.join(recorded.ROOT, "paper_1801_03863_amd", "csrc")
+    exe = str(tmp_path / "offsets")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + csrc, str(src), "-o", exe],
+                   check=True)
+    got = [int(v) for v in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()]
+    assert got == [((ny - 1) * p + nx - 1) * e for nx, ny, p, e in cases]
+    assert max(got) >= 1 << 32
