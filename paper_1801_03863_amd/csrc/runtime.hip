@@ -356,16 +356,14 @@ hipError_t launch_step(const lbm_ctx *c, int variant, const void *src, void *dst
 }
 
 // Tile of on-chip window shape v for a lattice, and the steps a launch
-// takes: the shape's count, halved until a window of that many steps fits
-// (one step always does: its window is the tile).
+// takes: the shape's count, halved until a window of that many steps fits, or
+// one, which needs no window (such a launch is shape 0's).
 int window_plan(const lbm_params_t &p, int v, lbm::WindowTile *tile)
 {
     const int st = storage_of(p.precision);
     for (int k = lbm::d2q9_variant_steps(p.collision, v); k > 1; k /= 2)
         if (lbm::d2q9_window_plan(st, p.collision, p.nx, p.ny, p.bc, k, tile, nullptr)) return k;
-    *tile = lbm::WindowTile{std::min(p.nx, 32), std::min(p.ny, 28), 0, 0};
-    tile->gx = (p.nx + tile->tw - 1) / tile->tw;
-    tile->gy = (p.ny + tile->th - 1) / tile->th;
+    *tile = lbm::WindowTile{};
     return 1;
 }
 

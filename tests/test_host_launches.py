@@ -47,3 +47,41 @@ def test_store_offsets_of_planes_beyond_4_gib(tmp_path):
     got = [int(v) for v in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()]
     assert got == [((ny - 1) * p + nx - 1) * e for nx, ny, p, e in cases]
     assert max(got) >= 1 << 32
+
+
+@pytest.mark.parametrize("coll", ["minxent4", "mrt"])
+def test_one_step_of_a_window_shape_is_shape_0s(run, coll):
+    # small lattices, where windows of several steps exist, and lattices too
+    # tall or too large for one
+    run("""
+    for prec, nx, ny in (("fp64", 17, 17), ("fp32", 257, 400), ("fp64", 3, 2000000), ("fp16dev", 64, 1900000),
+                         ("fp64", 24000, 24000)):
+        c = single("d2q9", %r, "cavity", prec, nx, ny)
+        B.lbm_set_variant(c, 0)
+        kernels()
+        B.lbm_step(c, 1)
+        one = kernels()
+        assert [k[0] for k in one] == ["k_d2q9"]
+        found = shapes(c, "window")
+        assert found
+        for v in found:
+            B.lbm_set_variant(c, v)
+            B.lbm_step(c, 1)
+            assert kernels() == one, (nx, ny, v)
+            n = B.lbm_variant_steps(c, v)
+            assert (n > 1) == (nx * ny < 200000), (nx, ny, n)
+            B.lbm_step(c, 2 * n + 1)
+            ks = kernels()
+            assert [k[0] for k in ks] == ["k_d2q9_win" if n > 1 else "k_d2q9"] * 2 + ["k_d2q9"]
+        B.lbm_free(c)
+    """ % coll)
+
+
+@pytest.mark.parametrize("prec,nx,ny", [("fp64", 3, 2000000), ("fp16dev", 64, 1900000)])
+def test_tall_lattices_can_be_tuned(run, prec, nx, ny):
+    run("""
+    c = single("d2q9", "srt", "box", %r, %d, %d)
+    assert 0 <= B.lbm_autotune(c, None) < B.lbm_variant_count(c)
+    B.lbm_step(c, 5)
+    B.lbm_free(c)
+    """ % (prec, nx, ny))
