@@ -177,8 +177,9 @@ int lbm_set_graph_chunk(lbm_ctx_t *ctx, int32_t chunk);
  * A single lattice whose planes hold at least 1 MiB also has its plane pad
  * tuned (see lbm_set_plane_pad) together with the two fastest shapes, and
  * the fastest (shape, pad) pair is kept; the cache line then carries the
- * pad too.  Synchronises.  For a batch, shapes with another tile
- * size rebuild the tile tables (a device allocation). */
+ * pad too.  A call that fails leaves the context in the shape it had.
+ * Synchronises.  For a batch, shapes with another tile size rebuild the tile
+ * tables (a device allocation). */
 int lbm_autotune(lbm_ctx_t *ctx, const char *cache_path, int32_t *chosen);
 
 /* Plane pad of a single lattice whose planes hold at least 1 MiB.  The b

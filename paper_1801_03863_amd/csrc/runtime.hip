@@ -1069,9 +1069,8 @@ const char *lbm_variant_name(const lbm_ctx_t *c, int32_t v)
     return c->b == 9 ? lbm::d2q9_variant_name(c->p.collision, v) : lbm::d1q3_variant_name(v);
 }
 
-int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
+static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
 {
-    if (!c) return fail(LBM_EINVAL, "null context");
     char key[256];
     std::snprintf(key, sizeof(key), "%s|%s|lat%d|prec%d|coll%d|bc%d|n%d|%dx%d|nodes%lld", LBM_SOURCE_ID,
                   c->arch.c_str(), c->b, c->p.precision, c->p.collision, c->p.bc, c->n, c->inst[0].nx,
@@ -1099,9 +1098,16 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
             }
         }
     }
-    hipEvent_t e0, e1;
-    HIPCHK(hipEventCreate(&e0));
-    HIPCHK(hipEventCreate(&e1));
+    struct Events {
+        hipEvent_t e[2] = {};
+        ~Events()
+        {
+            for (hipEvent_t x : e)
+                if (x) (void)hipEventDestroy(x);
+        }
+    } ev;
+    for (hipEvent_t &x : ev.e) HIPCHK(hipEventCreate(&x));
+    const hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
     const int nv = variant_count(c);
     // Enough launches per shape to time at least ~2e8 node updates.
     const int reps = (int)std::max<int64_t>(3, std::min<int64_t>(50, 200000000 / std::max<int64_t>(1, c->nodes)));
@@ -1223,8 +1229,6 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
         int rc = set_pad(c, kPadCandidates[kb]);
         if (rc) return rc;
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     int rc = lbm_set_variant(c, best_v);
     if (rc) return rc;
     if (cache_path) {
@@ -1236,6 +1240,19 @@ int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
     }
     if (chosen) *chosen = best_v;
     return LBM_OK;
+}
+
+int lbm_autotune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
+{
+    if (!c) return fail(LBM_EINVAL, "null context");
+    const int before = c->variant;
+    const int rc = tune(c, cache_path, chosen);
+    if (rc) {  // back to the shape it had, with the first error's message
+        const std::string msg = g_err;
+        (void)lbm_set_variant(c, before);
+        std::snprintf(g_err, sizeof(g_err), "%s", msg.c_str());
+    }
+    return rc;
 }
 
 int lbm_moments(lbm_ctx_t *c, double *rho, double *ux, double *uy)

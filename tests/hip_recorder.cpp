@@ -21,6 +21,7 @@ struct Launch {
 std::vector<Launch> launches;
 std::map<void *, size_t> blocks;
 hipError_t last = hipSuccess;
+long events = 0;  // alive
 long refuse_launch = -1;  // launches until one is refused; -1: never
 int refuse_pinned = 0, refuse_threads = 0, refuse_device = 0;
 char device_symbol[256];
@@ -56,7 +57,8 @@ const char *rec_name(long i)
 }
 unsigned rec_grid(long i, int axis) { return axis == 0 ? launches[i].grid.x : launches[i].grid.y; }
 unsigned rec_block(long i, int axis) { return axis == 0 ? launches[i].block.x : launches[i].block.y; }
-long rec_blocks() { return (long)blocks.size(); }
+long rec_blocks() { return (long)blocks.size(); }  // allocations alive
+long rec_events() { return events; }
 void rec_refuse(long launch, int pinned, int threads, int device)
 {
     refuse_launch = launch;
@@ -129,9 +131,9 @@ hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, 
 hipError_t hipGraphDestroy(hipGraph_t g) { return free(g), hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return free(x), hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t *e) { return *e = (hipEvent_t)malloc(8), hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { return *e = (hipEvent_t)malloc(8), ++events, hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t e) { return free(e), hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { return free(e), --events, hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }

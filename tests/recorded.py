@@ -16,7 +16,7 @@ import ctypes, re, sys, types
 rec = ctypes.CDLL(%(recorder)r, ctypes.RTLD_GLOBAL)
 rec.rec_name.restype = ctypes.c_char_p
 rec.rec_name.argtypes = [ctypes.c_long]
-rec.rec_count.restype = rec.rec_blocks.restype = ctypes.c_long
+rec.rec_count.restype = rec.rec_blocks.restype = rec.rec_events.restype = ctypes.c_long
 rec.rec_grid.argtypes = rec.rec_block.argtypes = [ctypes.c_long, ctypes.c_int]
 rec.rec_grid.restype = rec.rec_block.restype = ctypes.c_uint
 rec.rec_refuse.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int]

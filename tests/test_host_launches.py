@@ -85,3 +85,31 @@ def test_tall_lattices_can_be_tuned(run, prec, nx, ny):
     B.lbm_step(c, 5)
     B.lbm_free(c)
     """ % (prec, nx, ny))
+
+
+@pytest.mark.parametrize("refused", [0, 150, 5000])
+def test_a_tuning_that_fails_leaves_the_shape(run, refused):
+    # `refused` launches into the tuning the runtime refuses one: the call fails,
+    # and the context goes on in the shape it had
+    run("""
+    for start in (None, 7):
+        c = single("d2q9", "minxent4", "cavity", "fp64", 700, 900)  # planes with a pad, states set aside
+        if start is not None:
+            B.lbm_set_variant(c, start)
+        kernels()
+        B.lbm_step(c, 24)
+        before, blocks = kernels(), rec.rec_blocks()
+        rec.rec_refuse(%d, 0, 0, 0)
+        try:
+            B.lbm_autotune(c, None)
+        except B.LbmError as e:
+            assert e.code == B.LBM_EHIP and "recorded error" in str(e)
+        else:
+            raise AssertionError("tuned")
+        rec.rec_refuse(-1, 0, 0, 0)
+        kernels()
+        B.lbm_step(c, 24)
+        assert kernels() == before
+        assert rec.rec_blocks() == blocks and rec.rec_events() == 0
+        B.lbm_free(c)
+    """ % refused)
