@@ -274,15 +274,24 @@ int build_tiles(lbm_ctx *c, int tile_nodes)
             }
         }
     }
+    // The new table takes the old one's place only once it is there.
+    const size_t bytes = ti.size() * sizeof(int32_t);
+    int32_t *d[2] = {};
+    hipError_t e = hipMalloc(&d[0], bytes);
+    if (e == hipSuccess) e = hipMalloc(&d[1], bytes);
+    if (e == hipSuccess) e = hipMemcpy(d[0], ti.data(), bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(d[1], tf.data(), bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // reported here, not by the next launch
+        for (int32_t *p : d)
+            if (p) (void)hipFree(p);
+        return hip_fail(e, "the batch's tile table");
+    }
     if (c->d_tile_inst) (void)hipFree(c->d_tile_inst);
     if (c->d_tile_first) (void)hipFree(c->d_tile_first);
-    c->d_tile_inst = nullptr;
-    c->d_tile_first = nullptr;
+    c->d_tile_inst = d[0];
+    c->d_tile_first = d[1];
     c->ntiles = (int)ti.size();
-    HIPCHK(hipMalloc(&c->d_tile_inst, ti.size() * sizeof(int32_t)));
-    HIPCHK(hipMalloc(&c->d_tile_first, tf.size() * sizeof(int32_t)));
-    HIPCHK(hipMemcpy(c->d_tile_inst, ti.data(), ti.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(c->d_tile_first, tf.data(), tf.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     c->tile_nodes = tile_nodes;
     return LBM_OK;
 }
@@ -1015,9 +1024,11 @@ int lbm_set_variant(lbm_ctx_t *c, int32_t v)
     if (!c->batch && c->b == 9) HIPCHK(lbm::prepare_d2q9_variant(c->storage, c->p.collision, v));
     if (c->batch && c->b == 9 && v != c->lds_variant)
         HIPCHK(lbm::prepare_batch_variant(c->storage, c->p.collision, v));
+    if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, c->p.collision, v) != c->tile_nodes) {
+        const int rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
+        if (rc) return rc;
+    }
     use_variant(c, v);
-    if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, c->p.collision, v) != c->tile_nodes)
-        return build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
     return LBM_OK;
 }
 

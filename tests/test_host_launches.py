@@ -113,3 +113,33 @@ def test_a_tuning_that_fails_leaves_the_shape(run, refused):
         assert rec.rec_blocks() == blocks and rec.rec_events() == 0
         B.lbm_free(c)
     """ % refused)
+
+
+@pytest.mark.parametrize("lattice,prec", [("d2q9", "fp32"), ("d1q3", "fp64")])
+def test_a_shape_whose_tiles_find_no_memory_is_not_set(run, lattice, prec):
+    run("""
+    lattice = %r
+    c = batch(lattice, "minxent4" if lattice == "d2q9" else "srt", "periodic", %r,
+              [(300, 200 if lattice == "d2q9" else 1), (70, 90 if lattice == "d2q9" else 1)])
+    for start in range(B.lbm_variant_count(c)):
+        B.lbm_set_variant(c, start)
+        kernels()
+        B.lbm_step(c, 12)
+        before, blocks = kernels(), rec.rec_blocks()
+        for v in range(B.lbm_variant_count(c)):
+            rec.rec_refuse(-1, 0, 0, 1)
+            try:
+                B.lbm_set_variant(c, v)
+            except B.LbmError as e:
+                assert e.code == B.LBM_EHIP
+                rec.rec_refuse(-1, 0, 0, 0)
+                B.lbm_step(c, 12)
+                assert kernels() == before, (start, v)
+            else:  # the same tiles: nothing to allocate
+                rec.rec_refuse(-1, 0, 0, 0)
+                B.lbm_set_variant(c, start)
+                kernels()
+        assert rec.rec_blocks() == blocks
+    B.lbm_free(c)
+    assert rec.rec_blocks() == 0
+    """ % (lattice, prec))
