@@ -492,20 +492,22 @@ struct Stage {
         slots = 0;
     }
 
-    // Slots for `bytes` in all, or those that are there if they are enough.
-    int ready(size_t bytes)
+    // Slots for `bytes` in all, or those that are there if they are enough; false
+    // if there is no pinned memory for them.
+    bool ready(size_t bytes)
     {
         const size_t slot = bytes <= kSlotBytes ? std::max(kMinSlotBytes, (bytes + 4095) / 4096 * 4096) : kSlotBytes;
         const int want = (int)std::min<size_t>(kSlots, (bytes + slot - 1) / slot);
-        if (slot_bytes >= slot && slots >= want) return LBM_OK;
+        if (slot_bytes >= slot && slots >= want) return true;
         drop();
         if (hipHostMalloc((void **)&mem, slot * want, hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
             mem = nullptr;
-            return fail(LBM_ENOMEM, "hipHostMalloc of %s failed", "the read-back slots");
+            (void)hipGetLastError();  // not the next launch's error
+            return false;
         }
         slot_bytes = slot;
         slots = want;
-        return LBM_OK;
+        return true;
     }
 };
 
@@ -597,14 +599,15 @@ int read_pieces(lbm_ctx *c, const Stage &stage, int64_t piece, Launch launch, Co
         if (e == hipSuccess) copy(lo(k), hi(k), slot(k));
         return e;
     };
-    if (n <= 3 || S < 4) {  // a few pieces: no threads
+    auto alone = [&] {  // this thread copies
         hipError_t e = hipSuccess;
         for (int64_t k = 0; k < n + S && e == hipSuccess; ++k) {
             if (k >= S && k - S < n) e = drain(k - S);
             if (k < n && e == hipSuccess) e = enqueue(k);
         }
         return finish(e);
-    }
+    };
+    if (n <= 3 || S < 4) return alone();  // a few pieces
     struct Shared {
         std::mutex mu;
         std::condition_variable cv;
@@ -647,7 +650,7 @@ int read_pieces(lbm_ctx *c, const Stage &stage, int64_t piece, Launch launch, Co
     } catch (...) {
         // fewer threads than asked for: the pieces wait for those there are
     }
-    if (threads.empty()) return fail(LBM_ENOMEM, "no thread for the host copies");
+    if (threads.empty()) return alone();
     for (int64_t k = 0; k < n; ++k) {
         if (k >= S) {
             std::unique_lock<std::mutex> l(sh.mu);
@@ -731,6 +734,42 @@ int load_state(lbm_ctx *c, const double *rho, const double *ux, const double *uy
     return e == hipSuccess ? LBM_OK : hip_fail(e, "state upload");
 }
 
+// The same without slots, for want of pinned memory: the values are gathered in
+// device memory, and the runtime copies them.
+int read_staged(lbm_ctx *c, double *rho, double *ux, double *uy, double *f)
+{
+    const int64_t total = c->nodes;
+    const size_t bytes = sizeof(double) * (size_t)total;
+    const void *buf = c->buf[c->cur];
+    double *d = nullptr;
+    hipError_t e = hipMalloc(&d, bytes * (size_t)(f ? c->b : 3));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_fail(e, "state read-back");
+    }
+    auto down = [&](double *to, const double *from, size_t n) {
+        if (e == hipSuccess && to) e = hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, c->stream);
+    };
+    if (f) {
+        for (int i = 0; i < c->n && e == hipSuccess; ++i) {
+            const int64_t g = c->node_prefix[i], m = (int64_t)c->inst[i].nx * c->inst[i].ny;
+            e = lbm::launch_gather(c->b, c->storage, node_range(c, g, g + m), buf, nullptr, nullptr, nullptr,
+                                   d + c->b * g, m, c->iscale, c->stream);
+        }
+        down(f, d, bytes * (size_t)c->b);
+    } else {
+        e = lbm::launch_gather(c->b, c->storage, node_range(c, 0, total), buf, d, d + total, d + 2 * total, nullptr, 0,
+                               c->iscale, c->stream);
+        down(rho, d, bytes);
+        down(ux, d + total, bytes);
+        down(uy, d + 2 * total, bytes);
+    }
+    const hipError_t e2 = hipStreamSynchronize(c->stream);
+    (void)hipFree(d);
+    if (e == hipSuccess) e = e2;
+    return e == hipSuccess ? LBM_OK : hip_fail(e, "state read-back");
+}
+
 // Read the state back as moments (any of rho, ux, uy may be null) or
 // populations.
 int read_state(lbm_ctx *c, double *rho, double *ux, double *uy, double *f)
@@ -741,8 +780,7 @@ int read_state(lbm_ctx *c, double *rho, double *ux, double *uy, double *f)
         ~Own() { drop(); }
     } own;
     Stage &stage = shared.owns_lock() ? g_stage : own;
-    int rc = stage.ready(sizeof(double) * (size_t)planes * (size_t)c->nodes);
-    if (rc) return rc;
+    if (!stage.ready(sizeof(double) * (size_t)planes * (size_t)c->nodes)) return read_staged(c, rho, ux, uy, f);
     const int64_t piece = piece_nodes(c, stage, planes);
     const void *buf = c->buf[c->cur];
     if (f)

@@ -143,3 +143,33 @@ def test_a_shape_whose_tiles_find_no_memory_is_not_set(run, lattice, prec):
     B.lbm_free(c)
     assert rec.rec_blocks() == 0
     """ % (lattice, prec))
+
+
+@pytest.mark.parametrize("lattice,sizes", [("d2q9", [(40, 30)]), ("d2q9", [(1201, 1003)]),
+                                           ("d2q9", [(9, 7), (700, 301), (64, 64)]), ("d1q3", [(900001, 1)])])
+@pytest.mark.parametrize("refused", ["pinned", "threads", "pinned and device"])
+def test_reading_back_without_pinned_memory_or_threads(run, lattice, sizes, refused):
+    # neither is needed: the call reads back some other way.  Without device
+    # memory for that either it fails, and leaves nothing behind for the next.
+    run("""
+    lattice, sizes, refused = %r, %r, %r
+    prec, coll = "fp32", "srt"
+    if len(sizes) == 1:
+        c = single(lattice, coll, "periodic", prec, *sizes[0])
+    else:
+        c = batch(lattice, coll, "periodic", prec, sizes)
+    blocks = rec.rec_blocks()
+    rec.rec_refuse(-1, "pinned" in refused, "threads" in refused, "device" in refused)
+    for read in (lambda: B.lbm_moments(c), lambda: B.lbm_get_populations(c, 9 if lattice == "d2q9" else 3)):
+        try:
+            read()
+        except B.LbmError as e:
+            assert refused == "pinned and device" and e.code == B.LBM_EHIP, e
+        else:
+            assert refused != "pinned and device"
+        B.lbm_step(c, 3)
+    rec.rec_refuse(-1, 0, 0, 0)
+    assert rec.rec_events() == 0 and ("pinned" not in refused or rec.rec_blocks() == blocks)
+    B.lbm_free(c)
+    assert rec.rec_blocks() == 0
+    """ % (lattice, sizes, refused))
