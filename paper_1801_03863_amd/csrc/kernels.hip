@@ -1837,22 +1837,6 @@ int batch_tile_nodes(int lattice, int coll, int v)
     return kShapesB9[k].blk * kShapesB9[k].npt;
 }
 
-// A wave of a register pipeline takes some 50 collisions one after another per
-// launch; one step per launch of a batch too small for two waves per SIMD does
-// not wait for that (22 thousand nodes of 12 lattices: 5,700 MLUPS against 1,600;
-// a quarter million of 8 cavities: 38,000 against 22,000).  Beyond, three steps
-// lead in FP64 and FP32 and two in the other forms, which are bound by issue
-// (128 cavities, 5.2 million nodes, MLUPS, one step per launch / two-step rings /
-// pipeline of two steps / of three: FP64 35,700 / 49,500 / 45,700 / 56,100, FP32
-// 71,000 / 84,300 / 88,300 / 94,700, FP32 storage / FP64 compute 63,500 / 58,700 /
-// 72,000 / 66,300, SRT FP32 69,000 / - / 93,600 / 124,000).
-int batch_default_variant(int st, int coll, int64_t waves)
-{
-    if (waves < 2048) return 0;
-    const bool three = st == ST_F64 || st == ST_F32;
-    return batch_variant_count(9, coll) - kNumB9Pipes + (three ? 3 : 1);
-}
-
 hipError_t prepare_batch_variant(int st, int coll, int v)
 {
     if (coll != CO_MINXENT4 || v < kNumB9One || v >= kFirstB9Pipe) return hipSuccess;
@@ -1886,16 +1870,25 @@ static int pipe_waves(int st, int coll, int k)
     return st == ST_F64 ? (newton ? 6 - k : 7 - k) : (st == ST_F32N64 && newton ? 4 : 6);
 }
 
+// Microseconds of one collision of a wave of a register pipeline: its latency,
+// and its issue.  Fitted with the fixed time and the rate of d2q9_pipe_rows to
+// 7,200 launches (60,000 nodes to 3500^2, 4 to 32 rows, every rule and form; off
+// by 5-9% rms).
+static double pipe_latency_us(int st, int coll)
+{
+    const double us[2][4] = {{0.65, 0.54, 0.55, 0.56}, {1.08, 0.98, 0.85, 0.89}};
+    return us[coll == CO_MINXENT4 || coll == CO_MINXENT2][st];
+}
+static double pipe_issue_us(int st, int coll)
+{
+    const double us[2][4] = {{0.40, 0.32, 0.22, 0.29}, {0.68, 0.63, 0.40, 0.45}};
+    return us[coll == CO_MINXENT4 || coll == CO_MINXENT2][st];
+}
+
 int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
 {
-    const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
     const int occ = pipe_waves(st, coll, k);
-    // Microseconds of one collision of a wave: its latency, and its issue.  Fitted
-    // with the fixed time and the rate below to 7,200 launches (60,000 nodes to
-    // 3500^2, 4 to 32 rows, every rule and form; off by 5-9% rms).
-    const double latency_of[2][4] = {{0.65, 0.54, 0.55, 0.56}, {1.08, 0.98, 0.85, 0.89}};
-    const double issue_of[2][4] = {{0.40, 0.32, 0.22, 0.29}, {0.68, 0.63, 0.40, 0.45}};
-    const double latency = latency_of[newton][st], issue = issue_of[newton][st];
+    const double latency = pipe_latency_us(st, coll), issue = pipe_issue_us(st, coll);
     const double elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
     const int w = 64 - 2 * (k - 1);
     const int64_t strips = (nx + w - 1) / w;
@@ -1918,6 +1911,59 @@ int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
     }
     if (us_per_step) *us_per_step = best / k;
     return rows;
+}
+
+// One step per launch or a register pipeline, by the estimates of both: which
+// one is faster turns on how full the tiles are.  A wave of a pipeline takes all
+// its rows and the k - 1 around them one after another, 64 columns wide whatever
+// the lattice holds, and a block of 256 nodes one collision.  Measured us per
+// step, one step per launch / pipeline of three (FP32) or two (FP16 deviations):
+// 1000 cavities of 100^2 FP32 227 / 108, 1100 of 17^2 11.5 / 22.6, 600 of 64^2 28.9 /
+// 40.4, 50 of 4 x 800 12.1 / 28.7, 1000 of them 513 / 327; 600 of 64^2 FP16 deviations
+// 24.0 / 41.7, 1000 of 100^2 128 / 107.  Three steps lead in FP64 and FP32 and two in
+// the other forms, which are bound by issue (128 cavities, 5.2 million nodes,
+// MLUPS, one step per launch / two-step rings / pipeline of two steps / of three:
+// FP64 35,700 / 49,500 / 45,700 / 56,100, FP32 71,000 / 84,300 / 88,300 / 94,700,
+// FP32 storage / FP64 compute 63,500 / 58,700 / 72,000 / 66,300, SRT FP32 69,000 / - /
+// 93,600 / 124,000).   The estimates are off by
+// 16-21% rms over 340 batches of 8 thousand to 12 million nodes, lattices of 3 to
+// 1000 columns, every rule and form, so the pipeline has to lead by 15%.  The time
+// is then 0.90 of that of one step per launch on average and at most 1.14 of it
+// (1.04 and 3.7 with a pipeline wherever the tiles make 2048 waves).
+int batch_default_variant(int st, int coll, const Inst *inst, int n)
+{
+    const bool newton = coll == CO_MINXENT4 || coll == CO_MINXENT2;
+    const int k = st == ST_F64 || st == ST_F32 ? 3 : 2;
+    const int v = batch_variant_count(9, coll) - kNumB9Pipes + (k == 3 ? 3 : 1);
+    const int w = 64 - 2 * (k - 1), rows = kShapesB9[shape_of_b9(coll, v)].rows;
+    const double elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
+    double nodes = 0, blocks = 0;  // of one step per launch
+    double bytes = 0, narrow = 0;  // lines of a plane; of them, in rows of 32 bytes and less
+    double tiles = 0, collisions = 0;
+    int tallest = 0;
+    for (int i = 0; i < n; ++i) {
+        const double nx = inst[i].nx, ny = inst[i].ny;
+        const double row = std::ceil(nx * elem / 128), strips = std::ceil(nx / w), t = std::ceil(ny / rows);
+        nodes += nx * ny;
+        blocks += std::ceil(nx * ny / 256);
+        bytes += ny * row * 128;
+        narrow += nx * elem <= 32 ? ny * row * 128 : 0;
+        tiles += strips * t;
+        collisions += strips * (k * ny + t * k * (k - 1));
+        tallest = std::max(tallest, std::min(inst[i].ny, rows));
+    }
+    const double node_ps[2][4] = {{16.7, 8.8, 8.2, 5.4}, {18.4, 8.5, 9.7, 6.6}};
+    // Bytes at the rate of what the caches hold, or of memory (narrow rows, whose
+    // stores fill sectors in part, at 3.6 TB/s).
+    const double moved = 18 * bytes < 350e6 ? 18 * bytes / 7.6e6 : 18 * (bytes + 0.4 * narrow) / 5.0e6;
+    const double issue = pipe_issue_us(st, coll);
+    const double one = soft_max(4.6 + std::max(node_ps[newton][st] * 1e-6 * nodes, blocks / kWindowCus * issue), moved);
+    const double mean = tiles / 4 / kWindowCus, whole = std::ceil(mean);
+    const double r = whole <= pipe_waves(st, coll, k) ? whole : mean + (st == ST_F64 ? 0.55 : 0.0);
+    const double longest = k * tallest + k * (k - 1);
+    const double compute = soft_max(longest * pipe_latency_us(st, coll), collisions / tiles * r * issue);
+    const double pipe = (4.8 + soft_max(compute, 9 * bytes * (2.1 + 0.6 * k / tallest) / 5.2e6)) / k;
+    return pipe < 0.85 * one ? v : 0;
 }
 
 namespace {

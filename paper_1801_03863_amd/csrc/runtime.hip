@@ -896,12 +896,8 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
         CK(hipMalloc(&c->d_inst, table + numbers));
         c->d_prefix = (int64_t *)((char *)c->d_inst + table);
         CK(hipMemcpy(c->d_inst, both.data(), table + numbers, hipMemcpyHostToDevice));
-        int v = lbm::d1q3_default_variant(1, c->nodes);
-        if (c->b == 9) {
-            int64_t waves = 0;
-            for (const Inst &in : c->inst) waves += (int64_t)((in.nx + 61) / 62) * ((in.ny + 15) / 16);
-            v = lbm::batch_default_variant(c->storage, c->p.collision, waves);
-        }
+        const int v = c->b == 9 ? lbm::batch_default_variant(c->storage, c->p.collision, c->inst.data(), n)
+                                : lbm::d1q3_default_variant(1, c->nodes);
         use_variant(c, v);
         rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
         if (rc) {

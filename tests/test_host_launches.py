@@ -173,3 +173,27 @@ def test_reading_back_without_pinned_memory_or_threads(run, lattice, sizes, refu
     B.lbm_free(c)
     assert rec.rec_blocks() == 0
     """ % (lattice, sizes, refused))
+
+
+@pytest.mark.parametrize("coll,prec,sizes,kernel", [
+    # tiles nearly empty, or a state the caches hold: one step per launch
+    ("minxent4", "fp64", [(4, 800)] * 41, "k_d2q9_batch"),
+    ("minxent4", "fp64", [(17, 17)] * 1100, "k_d2q9_batch"),
+    ("minxent4", "fp16dev", [(64, 64)] * 600, "k_d2q9_batch"),
+    ("mrt", "fp64", [(8, 512)] * 1000, "k_d2q9_batch"),
+    ("srt", "fp32", [(180, 180)] * 8, "k_d2q9_batch"),
+    ("minxent4", "fp64", [(3, 3)], "k_d2q9_batch"),
+    # full tiles of lattices that fill the chip: a register pipeline
+    ("minxent4", "fp32", [(300, 300)] * 30 + [(40, 500)] * 4, "k_d2q9_rp"),
+    ("minxent4", "fp64", [(32 + 15 * k // 4, 32 + 15 * k // 4) for k in range(128)], "k_d2q9_rp"),
+    ("minxent2", "fp32_newton64", [(300, 300)] * 60, "k_d2q9_rp"),
+    ("srt", "fp64", [(1000, 33)] * 150, "k_d2q9_rp")])
+def test_starting_shape_of_a_batch_goes_by_its_tiles(run, coll, prec, sizes, kernel):
+    run("""
+    c = batch("d2q9", %r, "cavity", %r, %r)
+    kernels()
+    B.lbm_step(c, 1)
+    ks = kernels()
+    assert [k[0] for k in ks] == [%r], ks
+    B.lbm_free(c)
+    """ % (coll, prec, sizes, kernel))
