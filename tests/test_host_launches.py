@@ -197,3 +197,20 @@ def test_starting_shape_of_a_batch_goes_by_its_tiles(run, coll, prec, sizes, ker
     assert [k[0] for k in ks] == [%r], ks
     B.lbm_free(c)
     """ % (coll, prec, sizes, kernel))
+
+
+def test_one_step_of_a_register_shape_is_shape_0s(run):
+    run("""
+    for prec, n in (("fp64", 30), ("fp32", 50000), ("fp16dev", 1000003), ("fp64", 10000000)):
+        c = single("d1q3", "srt", "tube", prec, n, 1)
+        kernels()
+        B.lbm_step(c, 33)
+        assert [k[0] for k in kernels()] == ["k_d1q3_regs", "k_d1q3"], n
+        for v in shapes(c, "nodes in registers"):
+            B.lbm_set_variant(c, v)
+            B.lbm_step(c, 1)
+            assert [k[0] for k in kernels()] == ["k_d1q3"], (n, v)
+            B.lbm_step(c, 34)
+            assert [k[0] for k in kernels()] == ["k_d1q3_regs"] * 2, (n, v)
+        B.lbm_free(c)
+    """)
