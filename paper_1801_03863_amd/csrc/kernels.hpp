@@ -135,11 +135,13 @@ hipError_t launch_d1q3_regs(int storage, int n, int batch, const void *src, void
 hipError_t launch_d2q9_lds(int storage, int coll, const void *src, void *dst, const StepArgs &a, int nsteps,
                            int block, size_t smem_bytes, hipStream_t s);
 // Batched shapes: count (MinxEnt4 D2Q9 batches also have two-step shapes),
-// steps per launch, nodes per tile of the tile table (negative for 2D tiles:
+// steps per launch, the shape whose kernel takes a launch of one step (0 for the
+// register shapes), nodes per tile of the tile table (negative for 2D tiles:
 // -(width * 4096 + rows)), name, the shape a D2Q9 batch of these n instances
 // starts in, and the host-side set-up before a shape's first launch.
 int batch_variant_count(int lattice, int coll);
 int batch_variant_steps(int lattice, int coll, int variant);
+int batch_one_step(int lattice, int coll, int variant);
 int batch_tile_nodes(int lattice, int coll, int variant);
 const char *batch_variant_name(int lattice, int coll, int variant);
 int batch_default_variant(int storage, int coll, const Inst *inst, int n);

@@ -160,6 +160,7 @@ struct lbm_ctx {
     int32_t *d_tile_inst = nullptr;
     int32_t *d_tile_first = nullptr;
     int ntiles = 0;
+    int ntiles_one = 0;  // tiles of one-step launches behind them, if those take another shape
     int tile_nodes = 0;  // nodes per tile of the current batched variant
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;
@@ -251,9 +252,9 @@ int check_batch(const lbm_params_t *p, int32_t n)
     return LBM_OK;
 }
 
-int build_tiles(lbm_ctx *c, int tile_nodes)
+// Tiles of every instance, in instance order (tile_nodes as batch_tile_nodes).
+void list_tiles(const lbm_ctx *c, int tile_nodes, std::vector<int32_t> &ti, std::vector<int32_t> &tf)
 {
-    std::vector<int32_t> ti, tf;
     if (tile_nodes < 0) {
         // 2D tiles of bx x rows nodes, row-major within each instance, recorded
         // as the tile's index ty * tiles_x + tx.
@@ -274,7 +275,18 @@ int build_tiles(lbm_ctx *c, int tile_nodes)
             }
         }
     }
-    // The new table takes the old one's place only once it is there.
+}
+
+// Tile table of a batch's shape v, and behind it shape 0's if launches of one
+// step take that.  The new table takes the old one's place only once it is there.
+int build_tiles(lbm_ctx *c, int v)
+{
+    std::vector<int32_t> ti, tf;
+    const int tile_nodes = lbm::batch_tile_nodes(c->b, c->p.collision, v);
+    list_tiles(c, tile_nodes, ti, tf);
+    const size_t first = ti.size();
+    const bool single = lbm::batch_one_step(c->b, c->p.collision, v) != v;
+    if (single) list_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, 0), ti, tf);
     const size_t bytes = ti.size() * sizeof(int32_t);
     int32_t *d[2] = {};
     hipError_t e = hipMalloc(&d[0], bytes);
@@ -291,11 +303,11 @@ int build_tiles(lbm_ctx *c, int tile_nodes)
     if (c->d_tile_first) (void)hipFree(c->d_tile_first);
     c->d_tile_inst = d[0];
     c->d_tile_first = d[1];
-    c->ntiles = (int)ti.size();
+    c->ntiles = (int)first;
+    c->ntiles_one = (int)(ti.size() - first);
     c->tile_nodes = tile_nodes;
     return LBM_OK;
 }
-
 
 void drop_graphs(lbm_ctx *c)
 {
@@ -419,6 +431,12 @@ hipError_t launch_steps_from(const lbm_ctx *c, int v, int n, int cur, const lbm:
 {
     lbm::StepArgs b = a;
     b.max_steps = n;
+    if (c->batch && n == 1 && c->ntiles_one > 0) {
+        b.tile_inst += c->ntiles;
+        b.tile_first += c->ntiles;
+        b.ntiles = c->ntiles_one;
+        v = lbm::batch_one_step(c->b, c->p.collision, v);
+    }
     return launch_step(c, v, c->buf[cur], c->buf[cur ^ 1], b, s);
 }
 
@@ -899,7 +917,7 @@ int create(const lbm_params_t *p, int32_t n, int batch, const double *rho, const
         const int v = c->b == 9 ? lbm::batch_default_variant(c->storage, c->p.collision, c->inst.data(), n)
                                 : lbm::d1q3_default_variant(1, c->nodes);
         use_variant(c, v);
-        rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
+        rc = build_tiles(c, v);
         if (rc) {
             destroy(c);
             return rc;
@@ -1059,7 +1077,7 @@ int lbm_set_variant(lbm_ctx_t *c, int32_t v)
     if (c->batch && c->b == 9 && v != c->lds_variant)
         HIPCHK(lbm::prepare_batch_variant(c->storage, c->p.collision, v));
     if (c->batch && v != c->lds_variant && lbm::batch_tile_nodes(c->b, c->p.collision, v) != c->tile_nodes) {
-        const int rc = build_tiles(c, lbm::batch_tile_nodes(c->b, c->p.collision, v));
+        const int rc = build_tiles(c, v);
         if (rc) return rc;
     }
     use_variant(c, v);
