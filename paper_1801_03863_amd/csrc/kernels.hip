@@ -1765,20 +1765,16 @@ int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
     const double node_ps[2][4] = {{16.7, 8.8, 8.2, 5.4}, {18.4, 8.5, 9.7, 6.6}};
     double best = soft_max(4.6 + node_ps[newton][st] * 1e-6 * nodes, nodes * 18 * elem / 6.2e6);
     int v = 0;
-    for (int k = 0; k < kNumWindows; ++k) {
-        WindowTile tile;
-        double us = 0;
-        if (d2q9_window_plan(st, coll, nx, ny, bc, kShapes[kFirstWindow + k].steps, &tile, &us) && us < best) {
-            best = us;
-            v = windows + k;
-        }
-    }
+    int steps[kNumWindows];
+    for (int k = 0; k < kNumWindows; ++k) steps[k] = kShapes[kFirstWindow + k].steps;
+    WindowTile tile;
+    const int window = d2q9_window_best(st, coll, nx, ny, bc, steps, kNumWindows, best, &tile, &best);
+    if (window >= 0) v = windows + window;
     // The shapes whose rows go by the lattice; more steps only if they gain more
     // than the estimates are off by (600^2 FP64: 9.5 us with two, 10.1 with three).
     for (int k = 0; k < 3; ++k) {
         double us = 0;
-        d2q9_pipe_rows(st, coll, nx, ny, kShapes[kFirstPipe + k].steps, &us);
-        if (us < 0.95 * best) {
+        if (d2q9_pipe_rows(st, coll, nx, ny, kShapes[kFirstPipe + k].steps, &us, 0.95 * best)) {
             best = us;
             v = windows + kNumWindows + k;
         }
@@ -1892,31 +1888,35 @@ static double pipe_issue_us(int st, int coll)
     return us[coll == CO_MINXENT4 || coll == CO_MINXENT2][st];
 }
 
-int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step)
+int d2q9_pipe_rows(int st, int coll, int nx, int ny, int k, double *us_per_step, double below)
 {
     const int occ = pipe_waves(st, coll, k);
     const double latency = pipe_latency_us(st, coll), issue = pipe_issue_us(st, coll);
     const double elem = st == ST_F64 ? 8 : (st == ST_F16DEV ? 2 : 4);
     const int w = 64 - 2 * (k - 1);
-    const int64_t strips = (nx + w - 1) / w;
-    double best = 0;
-    int rows = 1;
+    const int strips = (nx + w - 1) / w;
+    const double bytes = (double)nx * ny * 9 * elem;
+    double best = below * k;
+    int rows = 0;
     for (int h = 1; h <= 48; ++h) {
         if (h > ny) break;
-        const int64_t blocks = (strips * ((ny + h - 1) / h) + 3) / 4;
+        const int collisions = k * h + k * (k - 1);  // of one wave
+        if (4.8 + collisions * latency >= best) break;  // more rows take longer
+        const int blocks = (strips * ((ny + h - 1) / h) + 3) / 4;
         // Blocks per compute unit: whole while all are resident at once; on
         // average, and in FP64 half a block of tail, when they come and go.
-        const double mean = (double)blocks / kWindowCus, whole = std::ceil(mean);
-        const double r = whole <= occ ? whole : mean + (st == ST_F64 ? 0.55 : 0.0);
-        const double compute = (k * h + k * (k - 1)) * soft_max(latency, r * issue);  // collisions of one wave
-        const double memory = (double)nx * ny * 9 * elem * (2.1 + 0.6 * k / h) / 5.2e6;
+        const int whole = (blocks + kWindowCus - 1) / kWindowCus;
+        const double r = whole <= occ ? whole : (double)blocks / kWindowCus + (st == ST_F64 ? 0.55 : 0.0);
+        const double memory = bytes * (2.1 + 0.6 * k / h) / 5.2e6;
+        if (4.8 + std::max(collisions * r * issue, memory) >= best) continue;
+        const double compute = collisions * soft_max(latency, r * issue);
         const double us = 4.8 + soft_max(compute, memory);
-        if (best == 0 || us < best) {
+        if (us < best) {
             best = us;
             rows = h;
         }
     }
-    if (us_per_step) *us_per_step = best / k;
+    if (us_per_step) *us_per_step = rows ? best / k : 1e30;
     return rows;
 }
 

@@ -77,7 +77,7 @@ int d2q9_variant_count(int coll);
 const char *d2q9_variant_name(int coll, int variant);
 // Steps one launch of a single-lattice D2Q9 shape takes at most (1; 2 for the
 // temporally blocked shapes; more for the on-chip window shapes, where a
-// lattice may allow fewer: d2q9_window_plan; StepArgs::max_steps sets fewer),
+// lattice may allow fewer: d2q9_window_best; StepArgs::max_steps sets fewer),
 // whether it is a window shape, and the host-side set-up a shape needs before
 // its first launch (call outside stream capture).
 int d2q9_variant_steps(int coll, int variant);
@@ -91,23 +91,24 @@ hipError_t launch_d2q9_step(int storage, int coll, int variant, const void *src,
                             const StepArgs &a, hipStream_t s);
 hipError_t launch_d2q9_batch_step(int storage, int coll, int variant, const void *src, void *dst,
                                   const StepArgs &a, hipStream_t s);
-// On-chip window shapes (window.hip).  Nodes a window may hold; the tile for
-// launches of k steps of one lattice (false if no window of k steps fits)
-// with its estimated microseconds per step; and the launch (StepArgs::win holds the
-// tile, max_steps at most the k it was planned for).
+// On-chip window shapes (window.hip).  Nodes a window may hold; which of nk step
+// counts per launch takes the fewest microseconds per step on one lattice, the
+// first of equal ones, with that estimate and the tile (-1 if none of their windows
+// fits, or none takes less than `below`); and the launch (StepArgs::win holds
+// the tile, max_steps at most the count it was planned for).
 constexpr int kWindowCus = 256;  // compute units the tiles are spread over
 int d2q9_window_cap(int storage);
-bool d2q9_window_plan(int storage, int coll, int nx, int ny, int bc, int k, WindowTile *tile,
-                      double *us_per_step);
+int d2q9_window_best(int storage, int coll, int nx, int ny, int bc, const int *ks, int nk, double below,
+                     WindowTile *tile, double *us_per_step);
 hipError_t launch_d2q9_window(int storage, int coll, const void *src, void *dst, const StepArgs &a, hipStream_t s);
 // Register-pipeline shapes (pipeline.hip): whether a shape is one; the tile
 // rows for launches of k steps of one lattice, with the estimated
-// microseconds per step; and one launcher per collision rule, for
+// microseconds per step (no rows, and 1e30, if that is not less than `below`); and one launcher per collision rule, for
 // windows of k steps (2 to 4; a batch may take fewer, a single lattice takes
 // k) with tiles of a.tile_rows rows.
 bool d2q9_variant_pipe(int coll, int variant);
 int d2q9_variant_rows(int coll, int variant);  // fixed tile rows of such a shape, or 0: d2q9_pipe_rows
-int d2q9_pipe_rows(int storage, int coll, int nx, int ny, int k, double *us_per_step);
+int d2q9_pipe_rows(int storage, int coll, int nx, int ny, int k, double *us_per_step, double below = 1e30);
 hipError_t launch_d2q9_pipe_0(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,
                               hipStream_t s);
 hipError_t launch_d2q9_pipe_1(int storage, int k, int batch, const void *src, void *dst, const StepArgs &a,

@@ -383,7 +383,7 @@ int window_plan(const lbm_params_t &p, int v, lbm::WindowTile *tile)
 {
     const int st = storage_of(p.precision);
     for (int k = lbm::d2q9_variant_steps(p.collision, v); k > 1; k /= 2)
-        if (lbm::d2q9_window_plan(st, p.collision, p.nx, p.ny, p.bc, k, tile, nullptr)) return k;
+        if (lbm::d2q9_window_best(st, p.collision, p.nx, p.ny, p.bc, &k, 1, 1e30, tile, nullptr) == 0) return k;
     *tile = lbm::WindowTile{};
     return 1;
 }
@@ -415,13 +415,11 @@ int launch_steps(const lbm_ctx *c, int v)
 // Make v the context's shape (host bookkeeping only).
 void use_variant(lbm_ctx *c, int v)
 {
-    c->variant = -1;  // so that launch_steps() plans anew
+    c->variant = -1;  // so that launch_steps() does not answer for the shape before
     c->win = lbm::WindowTile{};
-    c->spl = launch_steps(c, v);
-    if (!c->batch && c->b == 9) {
-        if (lbm::d2q9_variant_window(c->p.collision, v)) window_plan(c->p, v, &c->win);
-        if (lbm::d2q9_variant_pipe(c->p.collision, v)) c->tile_rows = pipe_rows(c->p, v);
-    }
+    if (!c->batch && c->b == 9 && lbm::d2q9_variant_window(c->p.collision, v)) c->spl = window_plan(c->p, v, &c->win);
+    else c->spl = launch_steps(c, v);
+    if (!c->batch && c->b == 9 && lbm::d2q9_variant_pipe(c->p.collision, v)) c->tile_rows = pipe_rows(c->p, v);
     c->variant = v;
 }
 
@@ -1447,8 +1445,11 @@ int lbm_run_noalloc(const lbm_params_t *p, const double *rho, const double *ux, 
     a.fp16_iscale = iscale;
     // The shape a context would start with: none of those needs set-up or
     // memory, so all of them run here and under capture.
-    const int v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc)
-                         : lbm::d1q3_default_variant(0, nodes);
+    // (One step is shape 0's in all of them.)
+    int v = 0;
+    if (nsteps > 1)
+        v = b == 9 ? lbm::d2q9_default_variant(storage, p->collision, p->nx, p->ny, p->bc)
+                   : lbm::d1q3_default_variant(0, nodes);
     int spl = b == 9 ? 1 : lbm::d1q3_variant_steps(v);
     if (b == 9) {
         spl = lbm::d2q9_variant_window(p->collision, v) ? window_plan(*p, v, &a.win)

@@ -24,7 +24,7 @@
 // solve: 1950 cycles in FP64, 1000 for SRT) and, with more than one wave per
 // SIMD, VALU issue (1550 cycles a wave); about 2.1 us of a launch lie outside the
 // kernel and 1.5 us are its mapping and first loads.  The tile is chosen for
-// that (d2q9_window_plan).  Measured, us per step, FP64 cavities, one step per
+// that (d2q9_window_best).  Measured, us per step, FP64 cavities, one step per
 // launch -> windows: 32^2 4.5 -> 1.6, 128^2 4.6 -> 2.0, 257^2 6.1 -> 3.6, 512^2
 // 10.3 -> 8.1; SRT tubes 33 x 27 3.0 -> 1.1, 129 x 123 3.2 -> 1.5.
 #include <hip/hip_runtime.h>
@@ -259,7 +259,8 @@ int win_extent(int t, int n, bool whole, bool wrap, int d)
 
 int d2q9_window_cap(int st) { return (int)std::min<size_t>(1024, 65536 / (9 * elem_of(st))); }
 
-bool d2q9_window_plan(int st, int coll, int nx, int ny, int bc, int k, WindowTile *out, double *us_per_step)
+int d2q9_window_best(int st, int coll, int nx, int ny, int bc, const int *ks, int nk, double below, WindowTile *out,
+                     double *us_per_step)
 {
     // Time of a launch in us: a fixed part (launch, mapping, first loads), the
     // lattice's bytes at the rate of launches whose state the caches hold, and
@@ -275,35 +276,64 @@ bool d2q9_window_plan(int st, int coll, int nx, int ny, int bc, int k, WindowTil
     const int simd_waves = newton && (st == ST_F64 || st == ST_F32N64) ? 4 : (newton || st == ST_F64 ? 7 : 8);
     const int cap = d2q9_window_cap(st);
     const bool xw = bc == BC_PERIODIC, yw = bc == BC_PERIODIC || bc == BC_TUBE;
-    double best = 0;
+    // Grids of tiles: for each width, the fewest rows that give each compute unit
+    // r blocks.
+    struct Grid {
+        WindowTile t;
+        int blocks, waves;  // of a compute unit; of a tile
+    } grids[16 * 6];
+    int n = 0;
     for (const int tw0 : {nx, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 40, 48, 64}) {
         if (tw0 > nx) break;
         const int gx = (nx + tw0 - 1) / tw0, tw = (nx + gx - 1) / gx;
-        // Rows: the fewest that give each compute unit r blocks.
-        for (int r = 1; r <= 6; ++r) {
+        if (tw > cap || (n && grids[n - 1].t.tw == tw)) continue;
+        for (int r = 1, last = 0; r <= 6; ++r) {
             const int gy0 = std::max(1, std::min(ny, kWindowCus * r / gx));
             const int th = (ny + gy0 - 1) / gy0, gy = (ny + th - 1) / th;
-            if (win_extent(tw, nx, gx == 1, xw, k - 1) * (int64_t)win_extent(th, ny, gy == 1, yw, k - 1) > cap) continue;
-            const int m0 = win_extent(tw, nx, gx == 1, xw, k - 1) * win_extent(th, ny, gy == 1, yw, k - 1);
-            const int resident = std::max(1, std::min((int)(163840 / (9 * elem_of(st) * m0)),
-                                                      4 * simd_waves / ((m0 + 63) / 64)));
-            double c = fixed;
-            for (int left = (int)(((int64_t)gx * gy + kWindowCus - 1) / kWindowCus); left > 0; left -= resident) {
-                const int blocks = std::min(left, resident);
-                for (int d = k - 1; d >= 0; --d) {
-                    const int m = win_extent(tw, nx, gx == 1, xw, d) * win_extent(th, ny, gy == 1, yw, d);
-                    c += exchange + issue * std::max(1.0, blocks * ((m + 63) / 64) / 4.0);
-                }
-                if (best != 0 && c >= best) break;
-            }
-            if (best == 0 || c < best) {
-                best = c;
-                *out = WindowTile{tw, th, gx, gy};
-            }
+            if (gy == last) continue;
+            last = gy;
+            if ((int64_t)tw * th > cap) continue;
+            const int blocks = (int)(((int64_t)gx * gy + kWindowCus - 1) / kWindowCus);
+            grids[n++] = Grid{WindowTile{tw, th, gx, gy}, blocks, (tw * th + 63) / 64};
         }
     }
-    if (us_per_step) *us_per_step = best / k;
-    return best > 0;
+    // The no-allocation call plans on every call, so a grid is left as soon as its
+    // steps cannot be cheap enough, without its windows at first (the choice of a
+    // starting shape, us of host time with every grid summed up / so: 17^2 15 / 1.8,
+    // 128^2 11 / 3.4, 257^2 13 / 3.8, 1000^2 5.5 / 1.7).
+    int found = -1;
+    for (int i = 0; i < nk; ++i) {
+        const int k = ks[i];
+        double best = below * k;
+        for (const Grid *g = grids; g < grids + n; ++g) {
+            const int tw = g->t.tw, th = g->t.th;
+            const bool wx = g->t.gx == 1, wy = g->t.gy == 1;
+            const double work = issue * g->blocks * g->waves / 4.0;
+            if (fixed + k * (exchange + std::max(issue, work)) * (1 - 1e-9) >= best) continue;
+            const int64_t m0 = (int64_t)win_extent(tw, nx, wx, xw, k - 1) * win_extent(th, ny, wy, yw, k - 1);
+            if (m0 > cap) continue;
+            const int resident = std::max(1, std::min((int)(163840 / (9 * elem_of(st) * m0)),
+                                                      4 * simd_waves / (int)((m0 + 63) / 64)));
+            const int turns = (g->blocks + resident - 1) / resident;
+            if (fixed + k * (turns * exchange + std::max(turns * issue, work)) * (1 - 1e-9) >= best) continue;
+            double c = fixed;
+            for (int left = g->blocks; left > 0 && c < best; left -= resident) {
+                const int blocks = std::min(left, resident);
+                for (int d = k - 1; d >= 0 && c < best; --d) {
+                    const int m = win_extent(tw, nx, wx, xw, d) * win_extent(th, ny, wy, yw, d);
+                    c += exchange + issue * std::max(1.0, blocks * ((m + 63) / 64) / 4.0);
+                }
+            }
+            if (c < best) {
+                best = c;
+                found = i;
+                *out = g->t;
+            }
+        }
+        below = std::min(below, best / k);
+    }
+    if (us_per_step && found >= 0) *us_per_step = below;
+    return found;
 }
 
 hipError_t launch_d2q9_window(int st, int coll, const void *src, void *dst, const StepArgs &a, hipStream_t s)

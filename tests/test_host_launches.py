@@ -252,3 +252,50 @@ def test_one_step_of_a_batch_is_shape_0s(run, lattice, coll, prec):
     B.lbm_free(c)
     assert rec.rec_blocks() == 0
     """ % (lattice, coll, prec))
+
+
+# Rule, form, boundary, size; launches of 192 steps, kernel, grid and block of the
+# first: what the search over every tile and row count finds.
+STARTING_SHAPES = [
+    ('srt', 'fp32_newton64', 'box', 3, 3, 3, 'k_d2q9_win', 1, 3, 64),
+    ('srt', 'fp32', 'cavity', 3, 3, 3, 'k_d2q9_win', 1, 3, 64),
+    ('mrt', 'fp64', 'periodic', 17, 17, 12, 'k_d2q9_win', 1, 17, 576),
+    ('minxent4', 'fp16dev', 'box', 17, 17, 3, 'k_d2q9_win', 1, 17, 320),
+    ('minxent4', 'fp16dev', 'box', 32, 32, 24, 'k_d2q9_win', 8, 32, 320),
+    ('minxent4', 'fp32_newton64', 'periodic', 32, 32, 24, 'k_d2q9_win', 8, 32, 320),
+    ('minxent4', 'fp64', 'cavity', 800, 4, 12, 'k_d2q9_win', 200, 1, 192),
+    ('minxent4', 'fp16dev', 'box', 800, 4, 3, 'k_d2q9_win', 200, 1, 576),
+    ('srt', 'fp32_newton64', 'box', 4, 800, 3, 'k_d2q9_win', 1, 200, 576),
+    ('srt', 'fp32', 'cavity', 4, 800, 3, 'k_d2q9_win', 1, 200, 576),
+    ('minxent4', 'fp32_newton64', 'periodic', 100, 100, 24, 'k_d2q9_win', 25, 10, 448),
+    ('minxent4', 'fp16dev', 'box', 100, 100, 24, 'k_d2q9_win', 25, 10, 448),
+    ('minxent4', 'fp64', 'cavity', 257, 257, 32, 'k_d2q9_win', 22, 11, 768),
+    ('mrt', 'fp64', 'periodic', 257, 257, 32, 'k_d2q9_win', 22, 11, 768),
+    ('trt', 'fp16dev', 'tube', 400, 400, 48, 'k_d2q9_win', 25, 10, 1024),
+    ('minxent4', 'fp32_newton64', 'periodic', 400, 400, 48, 'k_d2q9_win', 25, 10, 1024),
+    ('srt', 'fp32_newton64', 'box', 500, 300, 48, 'k_d2q9_win', 25, 10, 960),
+    ('mrt', 'fp64', 'periodic', 500, 300, 32, 'k_d2q9_win', 36, 14, 768),
+    ('trt', 'fp16dev', 'tube', 600, 600, 32, 'k_d2q9_win', 30, 25, 1024),
+    ('minxent4', 'fp32_newton64', 'periodic', 600, 600, 192, 'k_d2q9', 3, 600, 256),
+    ('minxent4', 'fp16dev', 'box', 1000, 1000, 192, 'k_d2q9', 4, 1000, 256),
+    ('minxent4', 'fp32_newton64', 'periodic', 1000, 1000, 192, 'k_d2q9', 4, 1000, 256),
+    ('minxent4', 'fp64', 'cavity', 2048, 64, 48, 'k_d2q9_win', 256, 1, 896),
+    ('srt', 'fp32_newton64', 'box', 2048, 64, 48, 'k_d2q9_win', 256, 1, 896),
+    ('minxent4', 'fp16dev', 'box', 2048, 2048, 192, 'k_d2q9', 8, 2048, 256),
+    ('srt', 'fp32', 'cavity', 2048, 2048, 48, 'k_d2q9_rp', 972, 1, 256),
+    ('minxent4', 'fp32_newton64', 'periodic', 61, 3001, 48, 'k_d2q9_win', 4, 126, 704),
+    ('trt', 'fp16dev', 'tube', 61, 3001, 32, 'k_d2q9_win', 4, 126, 896),
+]
+
+
+def test_starting_shapes_are_those_of_the_whole_search(run):
+    # the search leaves candidates early; it has to find what it found without
+    run("""
+    for coll, prec, bc, nx, ny, launches, *first in %r:
+        c = single("d2q9", coll, bc, prec, nx, ny)
+        kernels()
+        B.lbm_step(c, 192)
+        ks = kernels()
+        assert len(ks) == launches and list(ks[0]) == first, (coll, prec, bc, nx, ny, len(ks), ks[0])
+        B.lbm_free(c)
+    """ % (STARTING_SHAPES,))
