@@ -173,7 +173,8 @@ int lbm_set_graph_chunk(lbm_ctx_t *ctx, int32_t chunk);
  * Candidates produce bitwise identical results.  If cache_path is not NULL
  * the choice is read from / appended to that text file, keyed by a hash of
  * the kernel sources, device, lattice, precision, collision, boundary and
- * size.  *chosen (may be NULL) receives the index of the chosen shape.
+ * size (a batch's by the sizes of its instances, apart from single lattices).
+ * *chosen (may be NULL) receives the index of the chosen shape.
  * A single lattice whose planes hold at least 1 MiB also has its plane pad
  * tuned (see lbm_set_plane_pad) together with the two fastest shapes, and
  * the fastest (shape, pad) pair is kept; the cache line then carries the

@@ -1132,10 +1132,17 @@ const char *lbm_variant_name(const lbm_ctx_t *c, int32_t v)
 
 static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
 {
-    char key[256];
-    std::snprintf(key, sizeof(key), "%s|%s|lat%d|prec%d|coll%d|bc%d|n%d|%dx%d|nodes%lld", LBM_SOURCE_ID,
-                  c->arch.c_str(), c->b, c->p.precision, c->p.collision, c->p.bc, c->n, c->inst[0].nx,
-                  c->inst[0].ny, (long long)c->nodes);
+    char key[256], size[96];
+    if (c->batch) {  // shapes of their own, timed on these sizes (FNV-1a over them)
+        uint64_t h = 0xcbf29ce484222325ull;
+        for (const Inst &in : c->inst)
+            for (const int32_t v : {in.nx, in.ny}) h = (h ^ (uint32_t)v) * 0x100000001b3ull;
+        std::snprintf(size, sizeof(size), "batch%d|sizes%016llx", c->n, (unsigned long long)h);
+    } else {
+        std::snprintf(size, sizeof(size), "n1|%dx%d", c->inst[0].nx, c->inst[0].ny);
+    }
+    std::snprintf(key, sizeof(key), "%s|%s|lat%d|prec%d|coll%d|bc%d|%s|nodes%lld", LBM_SOURCE_ID, c->arch.c_str(), c->b,
+                  c->p.precision, c->p.collision, c->p.bc, size, (long long)c->nodes);
     if (cache_path) {
         if (FILE *fh = std::fopen(cache_path, "r")) {
             char line[512];

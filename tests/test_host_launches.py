@@ -299,3 +299,18 @@ def test_starting_shapes_are_those_of_the_whole_search(run):
         assert len(ks) == launches and list(ks[0]) == first, (coll, prec, bc, nx, ny, len(ks), ks[0])
         B.lbm_free(c)
     """ % (STARTING_SHAPES,))
+
+
+def test_cache_keys_tell_contexts_apart(run, tmp_path):
+    # a lattice and a batch of it alone; batches of one first lattice and total
+    run("""
+    path, keys = %r, []
+    for k, (sizes, many) in enumerate((([(40, 30)], 0), ([(40, 30)], 1), ([(40, 30), (20, 60), (60, 40)], 1),
+                                       ([(40, 30), (40, 60), (60, 20)], 1))):
+        c = batch("d2q9", "srt", "box", "fp32", sizes) if many else single("d2q9", "srt", "box", "fp32", *sizes[0])
+        B.lbm_autotune(c, path)
+        B.lbm_free(c)
+        keys = [line.split()[0] for line in open(path)]
+        assert len(keys) == k + 1, keys
+    assert len(set(keys)) == len(keys)
+    """ % str(tmp_path / "cache.txt"))
