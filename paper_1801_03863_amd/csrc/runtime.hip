@@ -1176,7 +1176,17 @@ static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
     } ev;
     for (hipEvent_t &x : ev.e) HIPCHK(hipEventCreate(&x));
     const hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
-    const int nv = variant_count(c);
+    // The shapes to time: window shapes that plan alike launch the same, and those
+    // that no window fits launch as shape 0 does.
+    std::vector<int> shapes, window_steps{1};
+    for (int v = 0; v < variant_count(c); ++v) {
+        if (!c->batch && c->b == 9 && lbm::d2q9_variant_window(c->p.collision, v)) {
+            const int k = launch_steps(c, v);
+            if (std::find(window_steps.begin(), window_steps.end(), k) != window_steps.end()) continue;
+            window_steps.push_back(k);
+        }
+        shapes.push_back(v);
+    }
     // Enough launches per shape to time at least ~2e8 node updates.
     const int reps = (int)std::max<int64_t>(3, std::min<int64_t>(50, 200000000 / std::max<int64_t>(1, c->nodes)));
     // A state that the caches hold only in part is timed as a run moves it, from
@@ -1199,12 +1209,13 @@ static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
         aside.p = nullptr;
         (void)hipGetLastError();
     }
-    // Time `n` launches of shape v; best of `trials`, in ms per `reps` steps (a
-    // two-step shape takes two per launch).
+    // Time `n` launches of shape v, or as many as two steps each make if it takes
+    // more; best of `trials`, in ms per `reps` steps.
     auto time_launches = [&](int v, int n, int trials, float &out) -> int {
         const bool pers = c->batch && v == c->lds_variant;
         const int pn = n | 1;
         const int spl = launch_steps(c, v);
+        if (spl > 2) n = std::max(3, 2 * n / spl);
         float best_t = 1e30f;
         for (int trial = 0; trial < trials; ++trial) {
             int cur = c->cur;
@@ -1241,7 +1252,7 @@ static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
     };
     // Stage 1: every shape, a short warm-up then the best of three trials.
     std::vector<std::pair<float, int>> t1;
-    for (int v = 0; v < nv; ++v) {
+    for (const int v : shapes) {
         float ms = 0.0f;
         int rc = time_shape(v, 3, 1, ms);
         if (rc == LBM_OK) rc = time_shape(v, reps, 3, ms);

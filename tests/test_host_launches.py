@@ -314,3 +314,28 @@ def test_cache_keys_tell_contexts_apart(run, tmp_path):
         assert len(keys) == k + 1, keys
     assert len(set(keys)) == len(keys)
     """ % str(tmp_path / "cache.txt"))
+
+
+@pytest.mark.parametrize("coll,prec,nx,ny", [("srt", "fp32", 257, 257), ("minxent4", "fp64", 32, 32),
+                                             ("mrt", "fp64", 1500, 1500), ("minxent4", "fp16dev", 3000, 2000)])
+def test_tuning_times_each_launch_once(run, coll, prec, nx, ny):
+    # window shapes that plan alike, or that run as shape 0, are timed once; and
+    # shapes of several steps per launch take no more steps than those of two
+    run("""
+    nx, ny = %d, %d
+    c = single("d2q9", %r, "box", %r, nx, ny)
+    steps = {v: B.lbm_variant_steps(c, v) for v in range(B.lbm_variant_count(c))}
+    windows = {steps[v] for v in shapes(c, "window")} - {1}
+    timed = len(steps) - len(shapes(c, "window")) + len(windows)
+    kernels()
+    B.lbm_autotune(c, None)
+    ks = kernels()
+    B.lbm_free(c)
+    assert len({k for k in ks if k[0] == "k_d2q9_win"}) == len(windows)
+    # the first shape timed after the windows marks the end of their first trials
+    reps = max(3, min(50, 200000000 // (nx * ny)))
+    first = [k for k in ks[:next(i for i, k in enumerate(ks) if k[0] == "k_d2q9_rp")] if k[0] == "k_d2q9_win"]
+    assert len(first) == sum(3 + 3 * max(3, 2 * reps // k) for k in windows)
+    pads = 0 if nx * ny * 4 < 1 << 20 else 30
+    assert len(ks) <= timed * (6 + 3 * reps) + (48 + pads) * (4 * reps + 2) + 200, len(ks)
+    """ % (nx, ny, coll, prec))
