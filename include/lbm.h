@@ -167,9 +167,9 @@ int lbm_set_graph_chunk(lbm_ctx_t *ctx, int32_t chunk);
 /* Time the candidate launch shapes of the fused kernel on this context's own
  * buffers (the state is left unchanged) and keep the fastest: every shape
  * is timed, then the eight fastest again with longer trials taken in turn
- * over six rounds.  A state of 32 MiB or more is timed as a run moves it,
- * between both buffers, with a copy set aside in a temporary allocation of
- * that size; without memory for it, and below, from the current buffer alone.
+ * over six rounds.  The state is timed as a run moves it, between both buffers,
+ * with a copy set aside in a temporary allocation of one buffer's size, or
+ * without memory for that from the current buffer alone.
  * Candidates produce bitwise identical results.  If cache_path is not NULL
  * the choice is read from / appended to that text file, keyed by a hash of
  * the kernel sources, device, lattice, precision, collision, boundary and

@@ -1189,14 +1189,13 @@ static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
     }
     // Enough launches per shape to time at least ~2e8 node updates.
     const int reps = (int)std::max<int64_t>(3, std::min<int64_t>(50, 200000000 / std::max<int64_t>(1, c->nodes)));
-    // A state that the caches hold only in part is timed as a run moves it, from
-    // one buffer to the other and back, with a copy of the state set aside:
-    // read over and over from one buffer it would come from the caches (FP16
-    // deviations, 3001 x 2203, 119 MB a buffer: the shape chosen that way takes 55.1
-    // us per step, the one chosen this way 50.1).
-    // Smaller states are timed from the current buffer alone, which is never
-    // written (the persistent shape runs an odd number of steps, ending in the
-    // other one), and so are states whose copy finds no memory.
+    // States are timed as a run moves them, from one buffer to the other and back,
+    // with a copy of the state set aside: read over and over from one buffer they
+    // come from nearer caches, and other shapes win (us per step of the shape
+    // chosen that way / this way: FP64 257^2 3.71 / 3.32, 600^2 12.8 / 8.6, FP16
+    // deviations 3001 x 2203 55.1 / 50.1).  A state whose copy finds no memory is
+    // timed from the current buffer alone, which is then never written (the
+    // persistent shape runs an odd number of steps, ending in the other one).
     const size_t state_bytes = buffer_bytes(c->elems, c->elem);
     struct Aside {
         char *p = nullptr;
@@ -1205,7 +1204,7 @@ static int tune(lbm_ctx_t *c, const char *cache_path, int32_t *chosen)
             if (p) (void)hipFree(p);
         }
     } aside;
-    if (state_bytes >= ((size_t)32 << 20) && hipMalloc((void **)&aside.p, state_bytes) != hipSuccess) {
+    if (hipMalloc((void **)&aside.p, state_bytes) != hipSuccess) {
         aside.p = nullptr;
         (void)hipGetLastError();
     }

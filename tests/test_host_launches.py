@@ -339,3 +339,21 @@ def test_tuning_times_each_launch_once(run, coll, prec, nx, ny):
     pads = 0 if nx * ny * 4 < 1 << 20 else 30
     assert len(ks) <= timed * (6 + 3 * reps) + (48 + pads) * (4 * reps + 2) + 200, len(ks)
     """ % (nx, ny, coll, prec))
+
+
+@pytest.mark.parametrize("nx,ny", [(17, 17), (600, 600), (1500, 1500)])
+def test_tuning_moves_the_state_as_a_run_does(run, nx, ny):
+    # every timing sets the state aside and puts it back; without memory for the
+    # copy the tuner still answers, and writes the other buffer only
+    run("""
+    c = single("d2q9", "minxent4", "box", "fp64", %d, %d)
+    kernels()
+    B.lbm_autotune(c, None)
+    ks = [k[0] for k in kernels()]
+    timings = [i for i, k in enumerate(ks) if k == "k_copy"]
+    assert timings and len(timings) %% 2 == 0 and ks[0] == ks[-1] == "k_copy"
+    rec.rec_refuse(-1, 0, 0, 1)
+    assert 0 <= B.lbm_autotune(c, None) < B.lbm_variant_count(c)
+    assert "k_copy" not in [k[0] for k in kernels()]
+    B.lbm_free(c)
+    """ % (nx, ny))
