@@ -9,9 +9,8 @@ steps are also timed for the plain FP64 form; the headline form's field error
 against it is reported.
 
 One step = one pass of the fused update over all 16.8 M nodes; the launch
-shape the autotuner picks takes one or two steps per launch (the two-step
-shapes keep the intermediate step in on-chip memory; results are bitwise the
-same).  Inputs are resident in HBM before timing starts.  MLUPS = nodes *
+shape the autotuner picks may take several steps per launch (it keeps the steps
+between in registers or on-chip memory; results are bitwise the same).  Inputs are resident in HBM before timing starts.  MLUPS = nodes *
 timed steps / seconds / 1e6.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -38,7 +37,7 @@ BYTES_PER_LU = {"fp64": 144, "fp32": 72, "fp32_newton64": 72, "fp16dev": 36}
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "traffic_fused_kernels_bench_workloads.txt")
 PROFILE_VALU = os.path.join(ROOT, "profiles", "valu_fused_kernels_bench_workloads.txt")
-# The single-step shape quoted beside a two-step headline: 256 x 1 tiles,
+# The single-step shape quoted beside the headline: 256 x 1 tiles,
 # non-temporal loads of the unshifted planes and non-temporal stores, an
 # 8-wave register budget, raised issue priority while the loads issue.
 SINGLE_STEP_SHAPE = 25
@@ -233,7 +232,7 @@ def rel_errors(a, b, mask):
 
 def batched_cavities(B, torch, I, steps, warmup, tune_cache=None, graph_chunk=0):
     """512 cavities, sides log-uniform in [32, 512], Re uniform in [100, 1e4],
-    lid 0.1, FP32, one launch per step (replayed from HIP graphs when
+    lid 0.1, FP32, in the tuned shape (replayed from HIP graphs when
     graph_chunk > 0); error against the same batch in FP64."""
     import numpy as np
     insts = I.cavity_batch(count=512)
@@ -274,7 +273,7 @@ def moving_flow(B, torch, I, n, tau, steps, warmup, tune_cache):
 def launch_bound(B, torch, I, tune_cache):
     """The two small configurations, whose steps are a few microseconds of
     work: the 800-node D1Q3 shock tube (400 steps, FP64) and the 256^2 cavity
-    (20000 steps, FP64 and FP32), each timed with one launch per step and replayed
+    (20000 steps, FP64 and FP32), each timed with plain launches and replayed
     from captured HIP graphs of 100 steps (the whole run is one timed
     region; results are bitwise the same)."""
     out = {}

@@ -135,8 +135,8 @@ int lbm_init(const lbm_params_t *p, const double *rho, const double *ux, const d
  * precision. */
 int lbm_workspace_bytes_batch(const lbm_params_t *p, int32_t n, size_t *bytes);
 
-/* Create a batched context: n instances advanced together by one launch per
- * time step.  p: n parameter records; fields concatenated in instance order. */
+/* Create a batched context: n instances advanced together, a launch taking one
+ * time step of all of them or several (lbm_variant_steps).  p: n parameter records; fields concatenated in instance order. */
 int lbm_init_batch(const lbm_params_t *p, int32_t n, const double *rho, const double *ux,
                    const double *uy, void *dev_workspace, size_t ws_bytes, void *hip_stream,
                    lbm_ctx_t **out);
@@ -224,8 +224,8 @@ const char *lbm_variant_name(const lbm_ctx_t *ctx, int32_t variant);
  * registers; 32 for the D1Q3 shapes that keep the nodes in registers.  HBM
  * then sees one read and one write of every population per launch.
  * Results are bitwise equal to single steps, status records included;
- * lbm_step() and graph chunks run a remainder as a launch of fewer steps,
- * and a batch instance's step limit can end its steps inside a launch.  0 if
+ * lbm_step() and graph chunks run a remainder as a launch of fewer steps (of
+ * one: as shape 0 does, except in the temporally blocked shapes), and a batch instance's step limit can end its steps inside a launch.  0 if
  * ctx is NULL or variant out of range. */
 int lbm_variant_steps(const lbm_ctx_t *ctx, int32_t variant);
 

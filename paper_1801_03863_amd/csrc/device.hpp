@@ -346,20 +346,6 @@ __device__ __forceinline__ void push9_inst(uint64_t d, int64_t P, uint32_t o, co
     }
 }
 
-// Write the nine post-collision populations of node index i.
-template <int ST, bool NT = false>
-__device__ __forceinline__ void push9(typename Form<ST>::T *__restrict__ d, int64_t P, int i,
-                                      const typename Form<ST>::C (&f)[9], const typename Form<ST>::C (&ref)[9],
-                                      float scale)
-{
-    using T = typename Form<ST>::T;
-    char *b = (char *)d;
-    const int64_t PB = P * (int64_t)sizeof(T);
-    const uint32_t o = (uint32_t)i * (uint32_t)sizeof(T);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) store<ST, NT>((T *)(b + q * PB + o), f[q], ref[q], scale);
-}
-
 // Role collision of one D2Q9 node.  Returns bit 0 = unstable, bit 1 = guarded.
 template <int ST, int CO>
 __device__ __forceinline__ int node9(typename Form<ST>::C (&f)[9], int role, const Inst &in)
@@ -451,7 +437,6 @@ __device__ __forceinline__ void push_lid(typename Form<ST>::T *__restrict__ d, i
     push9_xy<ST, NT>(d, P, x, y, pitch, f, ref, scale);
 }
 
-// Wave-level status update: one atomic per wave and kind.
 // Key of an unstable event: the step in the high word (saturating at 2^32 -
 // 1), the node index (x + y nx within its instance) in the low word, so that
 // the smallest key is the first step's smallest node.

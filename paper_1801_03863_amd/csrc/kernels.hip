@@ -19,10 +19,12 @@
 // every population exactly once per step; they are bound by HBM bandwidth in
 // the FP64, FP32 and FP32-storage/FP64-compute forms, and by VALU issue (the
 // logarithms, reciprocals and 4 x 4 solve of the Newton step) when the
-// populations are FP16 deviations.  The multi-step kernels further down (two
-// D2Q9 steps, or up to 256 D1Q3 steps, per launch) keep the steps between in
-// LDS and read and write every population once per launch; HBM then no
-// longer bounds them.
+// populations are FP16 deviations.  The kernels that take several steps per
+// launch read and write every population once per launch, and HBM then no longer
+// bounds the MinxEnt rules: two D2Q9 steps with the rows between in LDS, or a
+// batch's small lattices whole in LDS (further down); up to 64 in windows in LDS
+// (window.hip); two to four with the rows between in registers (pipeline.hpp); up
+// to 32 D1Q3 steps with the nodes in registers (tube.hip).
 //
 // Slots of boundary nodes whose upstream node lies outside the lattice read a
 // clamped (in-bounds) location; their values are bounced outward and never
@@ -1776,14 +1778,14 @@ bool d2q9_variant_window(int coll, int v)
 // The longer of two times that overlap, a little more where they are close.
 static double soft_max(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 
-// One-step launches cost 4.6 us each and 18 ps per node (FP64 MinxEnt; 5-17 in
+// One-step launches cost 4.4 us each and 18 ps per node (FP64 MinxEnt; 5-17 in
 // the others), and the bytes of a step at 6.2 TB/s beyond the caches (FP64,
-// us per step: 6.1, 8.4, 11.2, 24.9, 55 and 110 at 257^2, 400^2, 600^2, 1000^2,
-// 1400^2 and 2048^2).  The window shapes take 1.6 us per step at 32^2, 2.0 at
-// 128^2, 3.6 at 257^2 and 7.5 at 480^2, so they lead up to about 550^2; the
+// us per step: 6.2, 8.4, 10.7, 24, 55 and 110 at 257^2, 400^2, 600^2, 1000^2,
+// 1400^2 and 2048^2).  The window shapes take 1.5 us per step at 32^2, 1.8 at
+// 128^2, 3.4 at 257^2 and 6.3 at 480^2, so they lead up to about 550^2; the
 // register pipelines lead from there on (FP64 MinxEnt4 / MRT, us per step:
-// 1000^2 21.6 / 16.5, 2048^2 61 / 50, 4096^2 221 / 157, against 24.9 / 24.1,
-// 110 / 109 and 430 / 432 for one step per launch).
+// 1000^2 18.8 / 12.0, 2048^2 60 / 50, 4096^2 221 / 157, against 24 / 24, 110 / 109
+// and 430 / 432 for one step per launch).
 int d2q9_default_variant(int st, int coll, int nx, int ny, int bc)
 {
     const int windows = d2q9_variant_count(coll) - kNumPipes - kNumWindows;
@@ -1849,10 +1851,10 @@ int batch_one_step(int lattice, int coll, int v)
 }
 int d1q3_variant_steps(int v) { return (v >= 0 && v < kNumShapes3) ? kShapes3[v].steps : 1; }
 
-// Us per step of a single lattice, FP64: 0.35 at 800 to 50000 nodes with 2
-// nodes per lane; 0.78 / 0.83 / 0.98 with 2 / 4 / 8 at 200000; 2.46 / 2.02 /
-// 2.17 at a million; batches of 8 and 63 million nodes run fastest with 8 (one
-// step per launch: 2.6 us up to 200000 nodes, 8.9 at a million).
+// Us per step of a single lattice, FP64: 0.33 to 0.35 at 800 to 50000 nodes with
+// 2 nodes per lane; 0.74 / 0.78 / 0.95 with 2 / 4 / 8 at 200000; 2.29 / 1.83 / 2.01
+// at a million; batches of 8 and 63 million nodes run fastest with 8 (one step per
+// launch: 3.7 us up to 200000 nodes, 8.6 at a million).
 int d1q3_default_variant(int batch, int64_t nodes)
 {
     const int i = nodes < 400000 ? 0 : (nodes < 3000000 ? 1 : 2);  // 2, 4 or 8 nodes per lane

@@ -56,8 +56,8 @@ struct StepArgs {
     DevStatus *status;      // one record per instance
     const int64_t *step_base;  // if not null, added to `step` on the error path
     const int32_t *tile_inst;  // batched: instance of each tile
-    const int32_t *tile_first; // batched: first node of each tile, or for two-step shapes the tile's index
-                               // ty * tiles_x + tx within its instance
+    const int32_t *tile_first; // batched: first node of each tile, or of 2D tiles (two-step shapes, register
+                               // pipelines) the index ty * tiles_x + tx within the instance
     int64_t step;
     int32_t bc;
     int32_t ntiles;

@@ -15,9 +15,9 @@
 // read and written there every step, with a barrier).  Nodes per lane: more
 // repeat fewer window nodes (64 of 64 N) and hide more latency, fewer spread a
 // short lattice over more waves; 16 need so many registers that too few waves
-// remain.  Measured, segments in LDS -> here: 4096 tubes FP64 472,000 -> 780,000
+// remain.  Measured, segments in LDS -> here: 4096 tubes FP64 472,000 -> 838,000
 // MLUPS, FP16 deviations 895,000 -> 1,050,000, 1024 tubes FP32 870,000 ->
-// 1,480,000; 800 nodes FP64 0.64 -> 0.36 us per step.
+// 1,480,000; 800 nodes FP64 0.64 -> 0.33 us per step.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,9 +38,11 @@ __device__ __forceinline__ bool stable3(double v) { return __builtin_amdgcn_clas
 __device__ __forceinline__ bool stable3(float v) { return __builtin_amdgcn_classf(v, 0x1e0); }
 
 // Register budget (waves per SIMD asked of the compiler): with eight FP64 nodes
-// per lane it otherwise takes 181 registers, 2 waves; at 3 waves the 1024-tube
-// batch runs at 808,000 MLUPS instead of 764,000, at 4 waves at 728,000.  No
-// budget helps the other forms.
+// per lane it otherwise takes 181 registers, 2 waves.  At 3 waves it spills 60
+// bytes a lane, stored and loaded once per launch (the 4096-tube batch then writes
+// 1.34 times its populations' bytes), and the 1024-tube batch still runs at 808,000
+// MLUPS instead of 764,000; at 4 waves at 728,000.  No budget helps the other
+// forms.
 constexpr int tube_waves(int st, int n) { return st == ST_F64 && n == 8 ? 3 : 1; }
 
 template <int ST, int N, bool BATCH>

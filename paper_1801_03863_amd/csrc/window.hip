@@ -25,8 +25,8 @@
 // SIMD, VALU issue (1550 cycles a wave); about 2.1 us of a launch lie outside the
 // kernel and 1.5 us are its mapping and first loads.  The tile is chosen for
 // that (d2q9_window_best).  Measured, us per step, FP64 cavities, one step per
-// launch -> windows: 32^2 4.5 -> 1.6, 128^2 4.6 -> 2.0, 257^2 6.1 -> 3.6, 512^2
-// 10.3 -> 8.1; SRT tubes 33 x 27 3.0 -> 1.1, 129 x 123 3.2 -> 1.5.
+// launch -> windows: 32^2 4.4 -> 1.5, 128^2 4.6 -> 1.8, 257^2 6.2 -> 3.4, 480^2 9.7 ->
+// 6.3, 512^2 10.8 -> 7.5; SRT tubes 33 x 27 4.0 -> 1.0, 129 x 123 4.1 -> 1.4.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
