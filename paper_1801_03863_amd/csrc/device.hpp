@@ -68,6 +68,20 @@ __device__ __forceinline__ typename Form<ST>::T to_storage(typename Form<ST>::C 
     else return T(v);
 }
 
+// The same on a path beside another that converts too (the lid's rows).  Where
+// such paths meet, the compiler otherwise takes the conversion out of both, and an
+// FP16 deviation is rounded to float first: a kernel with such a path then differs
+// from one without in the last bit of populations far from ref.  The empty
+// statement keeps the conversion here, beside its fma, and so the other path's.
+template <int ST>
+__device__ __forceinline__ typename Form<ST>::T to_storage_apart(typename Form<ST>::C v, typename Form<ST>::C ref,
+                                                                 float scale)
+{
+    typename Form<ST>::T t = to_storage<ST>(v, ref, scale);
+    if constexpr (ST == ST_F16DEV) asm("" : "+v"(t));
+    return t;
+}
+
 template <int ST, bool NT = false>
 __device__ __forceinline__ void store(typename Form<ST>::T *p, typename Form<ST>::C v, typename Form<ST>::C ref,
                                       float scale)
@@ -431,10 +445,10 @@ __device__ __forceinline__ void push_lid(typename Form<ST>::T *__restrict__ d, i
                                          const Inst &in, const typename Form<ST>::C (&ref)[9], float scale)
 {
     using C = typename Form<ST>::C;
-    C f[9];
+    typename Form<ST>::T v[9];
 #pragma unroll
-    for (int a = 0; a < 9; ++a) f[a] = C(in.lid[a]);
-    push9_xy<ST, NT>(d, P, x, y, pitch, f, ref, scale);
+    for (int a = 0; a < 9; ++a) v[a] = to_storage_apart<ST>(C(in.lid[a]), ref[a], scale);
+    push9_xy_st<ST, NT>(d, P, x, y, pitch, v);
 }
 
 // Key of an unstable event: the step in the high word (saturating at 2^32 -

@@ -465,7 +465,7 @@ void k_d2q9_t2(const typename Form<ST>::T *__restrict__ src_all, typename Form<S
     }
     T lid_st[9];
 #pragma unroll
-    for (int q = 0; q < 9; ++q) lid_st[q] = to_storage<ST>(C(in.lid[q]), ref[q], a.fp16_scale);
+    for (int q = 0; q < 9; ++q) lid_st[q] = to_storage_apart<ST>(C(in.lid[q]), ref[q], a.fp16_scale);
     sync();  // halo array complete
 
     // Iteration j: first step of window row j from raw (loaded in the

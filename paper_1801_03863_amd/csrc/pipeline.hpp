@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void k_d2q9_rp(const typename Form<ST>::T *__r
             // a table's values are read here, not kept in registers for every row
             if constexpr (BATCH) asm volatile("" : "+s"(v));
 #pragma unroll
-            for (int q = 0; q < 9; ++q) sv[q] = to_storage<ST>(C(v[q]), ref[q], a.fp16_scale);
+            for (int q = 0; q < 9; ++q) sv[q] = to_storage_apart<ST>(C(v[q]), ref[q], a.fp16_scale);
         };
 
         T raw[9];
